@@ -1391,8 +1391,8 @@ bool launch_brick(const ConvArgs& a, hipStream_t s) {
 }
 
 // Calls that conv3d_brick_kernel takes: output (and mask) such that 4 channels of a voxel are one access, no mask on a
-// float32 output, a halo within 2 GiB and rows of less than 2^24 channels (32-bit offsets), weights and halo within a CU's
-// LDS (up to 112 channels, or 128).
+// float32 output, every voxel of a halo within 2 GiB of its first (which may lie a slice, a row and a voxel before the
+// tensor) and rows of less than 2^24 channels (32-bit offsets), weights and halo within a CU's LDS (up to 128 channels).
 // Rows up to 8 voxels fill at most half of its 16: there it takes only what gains all the same, one held chunk or 64
 // channels and more (8^3: 64 -> 64 channels 10.0 us by conv3d_kernel and 7.4 us by this, 32 -> 32 5.3 and 5.5 us).
 // One chunk of 8 or 16 channels: held in registers, 4 waves, two buffers (16 -> 16 at 96^3: 15.4 us; 18.0 us with the
@@ -1401,11 +1401,12 @@ bool launch_brick(const ConvArgs& a, hipStream_t s) {
 // and 8 waves if those give most CUs a workgroup (48 -> 16 at 96^3: 50 us with 4 waves, 43 us with 8; 48 -> 48 at 24^3,
 // 54 workgroups of 8: 6.6 and 7.8 us).
 bool try_brick(const ConvArgs& a, hipStream_t s) {
-    const int64_t halo = (int64_t)a.vol.H * a.vol.W * a.in_stride * 2 * (kBrickD + 2);
+    const int64_t voxel = (int64_t)a.in_stride * 2, row = a.vol.W * voxel, slice = a.vol.H * row;
+    const int64_t halo = (kBrickD + 1) * slice + (a.vol.H < 9 ? a.vol.H : 9) * row + (a.vol.W < 17 ? a.vol.W : 17) * voxel + 64;
     const bool held = a.cin == 8 || a.cin == 16;
     if (!al(a.out, a.out_f32 ? 16 : 8) || a.out_stride % 4 || a.out_coff % 4 || (a.mask && a.out_f32) ||
         (a.mask && (!al(a.mask, 8) || a.mask_stride % 4 || a.mask_coff % 4 || a.mask_stride >= 1 << 24)) ||
-        a.out_stride >= 1 << 24 || halo >= (int64_t)1 << 31 ||
+        a.out_stride >= 1 << 24 || halo > (int64_t)1 << 31 ||
         (a.vol.W <= 8 && !held && a.cin < 64))
         return false;
     const learn::BrickShape rows8 = brick_shape(a.vol, 8);
