@@ -68,6 +68,7 @@ struct PlanDev {
     int32_t fc = 0, pitch = 0, groups = 1;  // kernel variant: frames per workgroup, most rows per item + 1, element groups
     int32_t n_wt = kWaves, split = 1;       // wave tiles and element groups of a workgroup
     int32_t cap_rows = 0;                   // most rows of an item
+    int64_t launch_units = 0;               // most workgroups of a launch
     int64_t n_vox = 0;                      // voxels (per-transmit output stride: n_vox * F)
 };
 

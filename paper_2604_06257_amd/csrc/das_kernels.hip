@@ -585,9 +585,21 @@ static hipError_t launch_k(const PlanDev& p, const void* iq, void* out, hipStrea
     const size_t win = (size_t)waves * wb;
     const size_t red = p.split > 1 ? (size_t)waves * NTX * FC * kLanes * sizeof(float2) : 0;
     const size_t sh = win > red ? win : red;
-    const dim3 grid((unsigned)((int64_t)p.kp.n_tiles * (kWaves / p.n_wt) * nchunk)), block(waves * kLanes);
-    hipLaunchKernelGGL((das_kernel<FC, DT, NTX, kOne, kPlanar>), grid, block, sh, s, p, iq, reinterpret_cast<float2*>(out),
-                       __builtin_ctz(p.n_wt), __builtin_ctz(halves), __builtin_ctz(p.split), wb, p.n_vox * p.kp.F);
+    const int64_t units = (int64_t)p.kp.n_tiles * (kWaves / p.n_wt) * nchunk;
+    auto launch = [&](const PlanDev& q, int64_t n) {
+        hipLaunchKernelGGL((das_kernel<FC, DT, NTX, kOne, kPlanar>), dim3((unsigned)n), dim3(waves * kLanes), sh, s, q, iq,
+                           reinterpret_cast<float2*>(out), __builtin_ctz(p.n_wt), __builtin_ctz(halves), __builtin_ctz(p.split), wb,
+                           p.n_vox * p.kp.F);
+    };
+    if (units <= p.launch_units) {
+        launch(p, units);
+    } else {
+        PlanDev q = p;
+        for (int64_t u = 0; u < units; u += p.launch_units) {
+            q.wg_unit = p.wg_unit + u;
+            launch(q, std::min(p.launch_units, units - u));
+        }
+    }
     return hipGetLastError();
 }
 
@@ -780,6 +792,10 @@ void choose_split(PlanDev& p, int chunks, int max_wave_window, double items_per_
     };
     // (wave tiles and groups stay powers of two)
     while (waves() * kLanes > kMaxThreads || lds() > kLdsBytes) (p.n_wt > 1 ? p.n_wt : p.split) /= 2;
+    // A launch of 2^32 threads and more wraps around.
+    p.launch_units = (((int64_t)1 << 32) - 1) / (waves() * kLanes) / 8 * 8;
+    if (const char* env = std::getenv("DAS_LAUNCH"))  // tuning override
+        if (const long n = std::atol(env); n > 0) p.launch_units = std::min<int64_t>(n, p.launch_units);
 }
 
 int list_variants(int32_t* out, int capacity) {
