@@ -157,7 +157,8 @@ typedef struct das_plan_info {
     int32_t tile_dims[3];      /* lattice points per tile along x, y, z (0 when
                                   the points are not a lattice)                */
     int32_t max_window;        /* largest per-tile sample window (rows)        */
-    int32_t kernel_fc;         /* kernel variant: frames per workgroup,        */
+    int32_t kernel_fc;         /* kernel variant: frames per workgroup (0, 0, 0:
+                                  the general kernel, far slower),             */
     int32_t kernel_pitch;      /*   most window rows per work item + 1 (0: only
                                       the LDS bounds them),                    */
     int32_t kernel_groups;     /*   element groups per tile, at least (a plan

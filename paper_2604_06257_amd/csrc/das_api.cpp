@@ -634,9 +634,10 @@ int das_plan_query(const das_plan* plan, das_plan_info* info) {
     info->processed_triples = plan->processed_triples;
     for (int a = 0; a < 3; ++a) info->tile_dims[a] = plan->tiling.tile_dims[a];
     info->max_window = plan->max_window;
-    info->kernel_fc = plan->dev.fc;
-    info->kernel_pitch = plan->dev.pitch;
-    info->kernel_groups = plan->dev.groups;
+    const bool general = plan->dev.kp.wide != 0;
+    info->kernel_fc = general ? 0 : plan->dev.fc;
+    info->kernel_pitch = general ? 0 : plan->dev.pitch;
+    info->kernel_groups = general ? 0 : plan->dev.groups;
     return DAS_OK;
 }
 

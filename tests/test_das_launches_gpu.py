@@ -7,7 +7,7 @@ import pytest
 import torch
 
 import paper_2604_06257_amd as das
-from tests.conftest import small_case
+from conftest import small_case
 
 pytestmark = pytest.mark.gpu
 
