@@ -279,28 +279,69 @@ static int check_params(const das_params* p) {
     return DAS_OK;
 }
 
-// Whether a plan leaves the kernels' fixed point (|sample coordinate| and |carrier cycles| below 2^19) or an item's
-// fields: bounds from the boxes of the points and of the elements and from the largest arrival time.
+// The fixed point's offsets of a plan (row_fix, fix_t0, fix_ph), and whether it leaves the fixed point's range or an item's
+// fields (the general kernel serves it then).
+//
+// Active pairs have their sample row in [-1, S).  Where that range fits the fixed point, coordinates outside it do no harm:
+// their high words lie above any row's or below (and a transmit part that is far below its sum is held finely enough up to
+// 2^21).  In a longer record rows are counted from the earliest that a point can reach, and all of them have to fit.  Phases
+// are counted from a cycle near the record's begin in time where the largest does not fit.
 static bool outside_fixed_point(const das_params& p, const std::vector<float>& vox, const std::vector<float>& elem,
-                                const std::vector<float>& tx) {
+                                const std::vector<float>& tx, das_kparams& kp) {
+    kp.row_fix = kDasFixHigh;
+    kp.fix_t0 = kDasFix - kp.t0fs;
+    kp.fix_ph = kDasFix;
     const double records = (double)p.n_tx * p.n_elem * p.n_samples * p.n_frames;  // item offsets: 48 bits of bytes
     if (p.n_elem > das::kMaxElem || p.n_tx > das::kMaxTx || records > 35184372088832.0) return true;
-    double far2 = 0.0;
-    for (int a = 0; a < 3; ++a) {
-        double lo[2] = {INFINITY, INFINITY}, hi[2] = {-INFINITY, -INFINITY};
-        const std::vector<float>* const sets[2] = {&vox, &elem};
-        for (int q = 0; q < 2; ++q)
-            for (size_t i = (size_t)a; i < sets[q]->size(); i += 3) {
-                lo[q] = std::min(lo[q], (double)(*sets[q])[i]);
-                hi[q] = std::max(hi[q], (double)(*sets[q])[i]);
-            }
-        const double d = vox.empty() ? 0.0 : std::max(hi[0] - lo[1], hi[1] - lo[0]);
-        far2 += d * d;
+    if (vox.empty()) return false;
+    double lo[3] = {INFINITY, INFINITY, INFINITY}, hi[3] = {-INFINITY, -INFINITY, -INFINITY};
+    for (size_t i = 0; i < elem.size(); ++i) {
+        lo[i % 3] = std::min(lo[i % 3], (double)elem[i]);
+        hi[i % 3] = std::max(hi[i % 3], (double)elem[i]);
     }
-    double t = 0.0;
-    for (float x : tx) t = std::max(t, (double)std::fabs(x));
-    const double far = std::sqrt(far2) / p.sound_speed, limit = 524288.0 - 8.0;
-    return !(std::fabs(p.t0) * p.fs + t * p.fs + far * p.fs < limit && (t + far) * p.f_demod < limit);
+    // time to the elements from a point, at most
+    auto reach = [&](size_t v) {
+        double d2 = 0.0;
+        for (size_t a = 0; a < 3; ++a) {
+            const double x = vox[3 * v + a], d = std::max(x - lo[a], hi[a] - x);
+            d2 += d * d;
+        }
+        return std::sqrt(d2) / p.sound_speed;
+    };
+    const size_t V = vox.size() / 3;
+    double far = 0.0;
+    for (size_t v = 0; v < V; ++v) far = std::max(far, reach(v));
+    const auto ends = std::minmax_element(tx.begin(), tx.end());
+    const double limit = 524288.0 - 8.0;
+    const double first = (double)*ends.first - p.t0, last = (double)*ends.second - p.t0;
+    // Whether an active pair's transmit part may be held too coarsely.
+    auto coarse = [&](double rate) {
+        if (far * rate < 4 * limit || first * rate > -limit) return false;
+        for (size_t i = 0; i < tx.size(); ++i) {
+            const double t = (double)tx[i] - p.t0;
+            if (!(t * rate > -limit) && (t + reach(i % V)) * p.fs > -2.0) return true;
+        }
+        return false;
+    };
+    double from = 0.0, to = p.n_samples;  // sample rows that active pairs, or all, lie in
+    if (p.n_samples > limit) {
+        from = std::min(std::max(0.0, std::floor(first * p.fs) - 1.0), to);
+        to = (last + far) * p.fs + 1.0;
+        if (!(first * p.fs - from > -limit && to - from < limit)) return true;
+        kp.row_fix = kDasFixHigh - (int)from;
+        kp.fix_t0 -= from;
+    } else if (coarse(p.fs)) {
+        return true;
+    }
+    const double big = std::max(std::fabs((double)*ends.first), std::fabs((double)*ends.second)) + far;
+    if (!(big * p.f_demod < limit)) {
+        const double cycles = std::rint((p.t0 + from / p.fs) * p.f_demod);
+        const double most = std::max(std::fabs((p.t0 + (from - 1.0) / p.fs) * p.f_demod - cycles),
+                                     std::fabs((p.t0 + to / p.fs) * p.f_demod - cycles));
+        if (!(most < limit) || coarse(p.f_demod)) return true;
+        kp.fix_ph -= cycles;
+    }
+    return false;
 }
 
 static bool plan_live(const das_plan* plan) {
@@ -450,8 +491,7 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
         if (elem[3 * k + 2] != elem[2]) kp.planar = 0;
     kp.z0 = kp.planar ? (double)elem[2] : 0.0;
 
-    kp.fix_t0 = kDasFix - kp.t0fs;
-    kp.wide = outside_fixed_point(*p, vox, elem, tx) ? 1 : 0;
+    kp.wide = outside_fixed_point(*p, vox, elem, tx, kp) ? 1 : 0;
 
     std::vector<double> elemd(4 * (size_t)E, 0.0);
     for (int64_t k = 0; k < E; ++k)

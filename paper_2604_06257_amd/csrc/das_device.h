@@ -15,8 +15,11 @@
 // One FP64 FMA then replaces the FMA, floor, subtraction, clamps and two
 // conversions of a floating-point split (FP64 instructions and conversions
 // issue at half the FP32 rate on gfx950: 60 against 95-117 lanes per CU-cycle
-// measured).  Plans whose geometry leaves +-2^19 samples or cycles take the
-// general form (das_wide_setup) in a kernel of its own.
+// measured).  What counts is the rows of the record and the phases that reach
+// them: whole rows and cycles are taken off so that they lie in +-2^19 (any time
+// base), and plans where they do not take the general form (das_wide_setup) in a
+// kernel of its own.  A coordinate outside the record may leave the range: its
+// high word then is no row of any window.
 //
 // Cost layout: what depends on the voxel alone (its coordinates in FP64, and for
 // arrays whose elements share one depth plane the depth terms of the distance and
@@ -43,7 +46,7 @@ struct das_rx {
     float w;    // apodization weight
 };
 
-// Transmit part: depends on (voxel, transmit) only; both offset by kDasFix.
+// Transmit part: depends on (voxel, transmit) only; both in fixed point.
 struct das_txc {
     double a;   // (tau_tx - t0) fs: sample coordinate of the transmit delay
     double b;   // fd tau_tx: carrier cycles of the transmit delay
@@ -53,7 +56,7 @@ constexpr float kDasFixUnit = 2.3283064e-10f;  // 2^-32
 
 // Per (voxel, element, transmit): what the multiply-accumulate needs.
 struct das_coef {
-    int hi;        // floor(u) + kDasFixHigh
+    int hi;        // floor(u) + row_fix
     float beta;    // u - floor(u)
     float cr, ci;  // w * exp(+j 2 pi fd tau)
 };
@@ -123,11 +126,11 @@ __device__ __forceinline__ das_rx das_rx_setup(const das_lane& L, double ex, dou
     return kp.planar ? das_rx_setup_t<true>(L, ex, ey, ez, kp) : das_rx_setup_t<false>(L, ex, ey, ez, kp);
 }
 
-__device__ __forceinline__ das_txc das_tx_const(float tx_arrival, double fix_t0, const das_kparams& kp) {
+__device__ __forceinline__ das_txc das_tx_const(float tx_arrival, double fix_t0, double fix_ph, const das_kparams& kp) {
     const double t = (double)tx_arrival;
     das_txc o;
     o.a = fma(t, kp.fs, fix_t0);
-    o.b = fma(t, kp.fd, kDasFix);
+    o.b = fma(t, kp.fd, fix_ph);
     return o;
 }
 
@@ -152,7 +155,7 @@ __device__ __forceinline__ das_coef das_wide_setup(const das_rx& rx, float tx_ar
     const double fl = floor(u);
     das_coef o;
     // rows far outside the record are never in a window
-    o.hi = (int)fmin(fmax(fl, -2.0), 536870912.0) + kDasFixHigh;
+    o.hi = (int)fmin(fmax(fl, -2.0), 536870912.0) + kp.row_fix;
     o.beta = (float)(u - fl);
     double ph = fma(rx.r, kp.fd_c, t * kp.fd);
     ph -= rint(ph);
@@ -165,5 +168,5 @@ __device__ __forceinline__ das_coef das_wide_setup(const das_rx& rx, float tx_ar
 // Whether a (voxel, element, transmit) triple contributes: weight > 0 and the delayed sample inside the
 // record (floor(u) in [-1, S - 1], with zero padding on both sides).
 __device__ __forceinline__ bool das_active(const das_rx& rx, const das_coef& c, const das_kparams& kp) {
-    return rx.w > 0.0f && (unsigned)(c.hi - (kDasFixHigh - 1)) <= (unsigned)kp.S;
+    return rx.w > 0.0f && (unsigned)(c.hi - (kp.row_fix - 1)) <= (unsigned)kp.S;
 }

@@ -16,12 +16,14 @@ struct das_kparams {
     double fs;
     double fd;
     double t0fs;         // t0 * fs
-    double fix_t0;       // the fixed-point offset less t0 * fs
+    double fix_t0;       // the fixed-point offset less t0 * fs and the rows that sample coordinates are counted from
+    double fix_ph;       // the fixed-point offset less a whole number of carrier cycles
+    int32_t row_fix;     // high word of a sample coordinate less this: the sample row
     float two_fnum;      // 2 f#
     float alpha;         // Tukey taper fraction
     float inv_2alpha;    // 1 / (2 alpha), 0 when alpha = 0
     float edge_2alpha;   // (1 - alpha) / (2 alpha), 0 when alpha = 0
     int32_t planar;      // every element lies in the plane z = z0
     double z0;           // that plane's depth (when planar)
-    int32_t wide;        // delays or phases outside the fixed point's range: the general kernel
+    int32_t wide;        // rows or phases outside the fixed point's range: the general kernel
 };

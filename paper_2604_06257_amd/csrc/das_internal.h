@@ -39,7 +39,7 @@ constexpr int lds_row_bytes(int fc) { return fc <= 2 ? 8 * fc : 8 * fc + 16; }
 //   x, y  offset of its first loaded sample (frame 0) in the channel data, in samples: 48 bits, bits 16-31 of y left
 //         to the rows loaded (bits 16-23: the window's rows and the one after them, less what lies past the record)
 //         and the window's rows (bits 24-31)
-//   z     the window's first row + kDasFixHigh (what the high word of a fixed-point sample coordinate is taken from);
+//   z     the window's first row + row_fix (the high word of a fixed-point sample coordinate in that row);
 //         a window that begins at row -1 loads from row 0
 //   w     element << 12 | transmit
 constexpr int kMaxElem = 1 << 20, kMaxTx = 1 << 12, kMaxRows = 254;
@@ -47,11 +47,11 @@ constexpr int kItemPad = 4;  // items past the end that a wave may read ahead
 #ifdef __HIPCC__
 __host__ __device__
 #endif
-inline int4 pack_item(int e, int t, int row, int rows, int E, int S, int F) {
+inline int4 pack_item(int e, int t, int row, int rows, int E, int S, int F, int row_fix) {
     const int from = row < 0 ? 0 : row, end = row + rows + 1 < S ? row + rows + 1 : S, loaded = end - from;
     const int64_t off = (((int64_t)t * E + e) * S + from) * F;
     return int4{(int)(uint32_t)off, (int)((uint32_t)(off >> 32) | (uint32_t)loaded << 16 | (uint32_t)rows << 24),
-                row + kDasFixHigh, (int)((uint32_t)e << 12 | (uint32_t)t)};
+                row + row_fix, (int)((uint32_t)e << 12 | (uint32_t)t)};
 }
 
 struct PlanDev {

@@ -102,12 +102,12 @@ __global__ __launch_bounds__(kSlots) void window_kernel(PlanDev p, int tile0, in
             const float txv = p.tx[((int64_t)wi * kp.T + t) * kLanes + lane];
             das_coef c;
             if constexpr (kWide) c = das_wide_setup(rx, txv, kp);
-            else c = das_tx_setup(rx, das_tx_const(txv, kp.fix_t0, kp), kp);
+            else c = das_tx_setup(rx, das_tx_const(txv, kp.fix_t0, kp.fix_ph, kp), kp);
             const bool act = valid && das_active(rx, c, kp);
             const unsigned long long ball = __ballot(act);
             int2 w = make_int2(0, 0);
             if (ball != 0) {
-                const int i0 = c.hi - kDasFixHigh;
+                const int i0 = c.hi - kp.row_fix;
                 int lo = act ? i0 : INT_MAX, hi = act ? i0 : INT_MIN;
                 for (int o = 32; o > 0; o >>= 1) {
                     lo = min(lo, __shfl_xor(lo, o));
@@ -187,7 +187,7 @@ __global__ __launch_bounds__(kLanes) void items_kernel(das_kparams kp, int tile0
             const int e = i / T, t = i - e * T;
             int4* dst = items + at + (before - pieces);
             for (int r = 0; r < x.y; r += cap)
-                *dst++ = pack_item(e, t, x.x + r, min(cap, x.y - r), E, kp.S, kp.F);
+                *dst++ = pack_item(e, t, x.x + r, min(cap, x.y - r), E, kp.S, kp.F, kp.row_fix);
         }
         at += __shfl(before, kLanes - 1);
     }
@@ -342,7 +342,7 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
 
     struct Item {
         uint64_t at;  // sample offset and row counts
-        int row;      // first row + kDasFixHigh
+        int row;      // first row + row_fix
         uint32_t et;  // element and transmit
         // (spelled out: the compiler would compare all 64 bits on the vector unit instead)
         __device__ int rows() const {
@@ -362,7 +362,7 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
     // Reads go through a buffer resource over the rows to load, whose range check returns zero outside it: for the
     // rows past the record's end, and for row -1 (whose offset wraps to one past the end), the record's zero
     // padding; and for the lanes past the window, which then fetch nothing.  Frames past F read the next row's and
-    // feed no output.
+    // feed no output.  (Where rows are not counted from 0, no window begins before the row they are counted from.)
     auto window = [&](const Item& it) {
         const uint64_t a = reinterpret_cast<uint64_t>(iq) + it.at * kEB;  // the low 48 bits count
         return __builtin_amdgcn_make_buffer_rsrc(reinterpret_cast<void*>(a), (short)0, it.loaded() * row_bytes,
@@ -419,9 +419,9 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
     };
     int last_e = -1;
     das_rx rx;
-    double fix_t0 = kp.fix_t0;
-    asm volatile("" : "+v"(fix_t0));  // an FMA takes one scalar operand: kept in vector registers
-    const das_txc tc0 = das_tx_const(p.tx[(int64_t)wi * kp.T * kLanes + lane], fix_t0, kp);  // transmit 0
+    double fix_t0 = kp.fix_t0, fix_ph = kp.fix_ph;
+    asm volatile("" : "+v"(fix_t0), "+v"(fix_ph));  // an FMA takes one scalar operand: kept in vector registers
+    const das_txc tc0 = das_tx_const(p.tx[(int64_t)wi * kp.T * kLanes + lane], fix_t0, fix_ph, kp);  // transmit 0
     struct Xyz {
         double x, y, z;
     };
@@ -445,7 +445,7 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
                 rx = das_rx_setup_t<kPlanar>(L, e.x, e.y, e.z, kp);
                 last_e = it.e();
             }
-            c = das_tx_setup(rx, das_tx_const(txv, fix_t0, kp), kp);
+            c = das_tx_setup(rx, das_tx_const(txv, fix_t0, fix_ph, kp), kp);
         }
         const unsigned d = (unsigned)c.hi - (unsigned)it.row;
         const unsigned r = d < (unsigned)it.rows() ? d : zero_row;
@@ -552,7 +552,7 @@ __global__ __launch_bounds__(kSlots) void das_wide_kernel(PlanDev p, const void*
                 if (!das_active(rx, c, kp)) continue;
                 const S* rec = reinterpret_cast<const S*>(iq) + ((int64_t)t * kp.E + e) * kp.S * kp.F + f;
                 float2 a = make_float2(0.0f, 0.0f), b = a;
-                const int i0 = c.hi - kDasFixHigh;
+                const int i0 = c.hi - kp.row_fix;
                 if (i0 >= 0) a = decode<DT>(rec[(int64_t)i0 * kp.F], 0);
                 if (i0 + 1 < kp.S) b = decode<DT>(rec[(int64_t)(i0 + 1) * kp.F], 0);
                 const float tr = fmaf(c.beta, b.x - a.x, a.x);

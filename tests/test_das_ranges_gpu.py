@@ -45,3 +45,64 @@ def test_rows_too_far_apart_take_the_general_kernel(T, F):
     iq = random_iq((T, 4, 600_000, F), seed=1)
     kernel, db = run(iq, elem, vox, tx)
     assert kernel == GENERAL and db <= -100.0
+
+
+@pytest.mark.parametrize("late", [0.0625, 0.25, -0.25, 40.0])
+@pytest.mark.parametrize("T,F,per_tx", [(1, 1, False), (2, 3, False), (3, 2, True)])
+def test_any_time_base_keeps_the_staged_kernel(late, T, F, per_tx):
+    """Arrival times and t0 on an absolute time base: millions of rows and carrier cycles, few of them between the two."""
+    elem = linear_array(9, 0.3e-3)
+    vox = column()
+    tx = np.stack([np.float32(late) + (vox[:, 2] / C + 1e-7 * t).astype(np.float32) for t in range(T)]).astype(np.float32)
+    kernel, db = run(random_iq((T, 9, 700, F), seed=11), elem, vox, tx, t0=late, per_tx=per_tx)
+    assert kernel != GENERAL and db <= -100.0
+
+
+@pytest.mark.parametrize("row,t0", [(0, 0.0), (150_000, 0.0), (598_700, 0.0), (598_700, 0.3), (-10, 0.0)])
+@pytest.mark.parametrize("T,F", [(1, 1), (2, 7)])
+def test_long_records_keep_the_staged_kernel(row, t0, T, F):
+    """A 600,000-row record of which a plan uses some rows: at its beginning (partly before it), within it, at its end (partly
+    past it)."""
+    elem = linear_array(4, 0.3e-3)
+    vox = column(step=3e-4)
+    tx = np.stack([np.float32(t0) + (vox[:, 2] / C + 1e-7 * t + row / FS).astype(np.float32) for t in range(T)]).astype(np.float32)
+    kernel, db = run(random_iq((T, 4, 600_000, F), seed=row + T + 20), elem, vox, tx, t0=t0)
+    assert kernel != GENERAL and db <= -100.0
+
+
+@pytest.mark.parametrize("f_number", [0.0, 0.8])
+def test_points_far_outside_the_record_keep_the_staged_kernel(f_number):
+    """Points and arrival times so far away that their sample coordinates leave the fixed point: exact zeros there, the
+    others' sums as without them, in the same waves."""
+    elem = linear_array(5, 0.3e-3)
+    vox = column(128)
+    tx = (vox[None, :, 2] / C).astype(np.float32)
+    vox[3::8, 2] = 1e4                        # 1.3e8 rows
+    vox[4::8, 0] = -3e7
+    vox[5::16, 2] = 2e19                      # the square of the distance is infinite in float32
+    tx[0, 6::16] = np.float32(3e38)
+    tx[0, 7::16] = np.float32(-3e38)
+    tx[0, 14::16] = 1.0
+    tx[0, 15::16] = -0.05
+    iq = random_iq((1, 5, 900, 3), seed=7)
+    p = das.Params(1, 5, 900, 3, 128, C, FS, FD, 0.0, f_number, 0.5)
+    with das.Plan(p, *(torch.from_numpy(a).cuda() for a in (elem, vox, tx))) as plan:
+        kernel = plan.info()["kernel"]
+        y = plan.execute(torch.from_numpy(iq).cuda()).cpu().numpy()
+    near = np.ones(128, bool)
+    for first, step in ((3, 8), (4, 8), (5, 16), (6, 16), (7, 16), (14, 16), (15, 16)):
+        near[first::step] = False
+    ref = oracle.das(iq, elem, vox[near], tx[:, near], c=C, fs=FS, fd=FD, t0=0.0, f_number=f_number, tukey_alpha=0.5)
+    assert kernel != GENERAL and np.abs(ref).min() > 0
+    assert np.all(y[~near] == 0) and oracle.nrmse_db(y[near], ref) <= -100.0
+
+
+def test_high_carrier_in_a_slowly_sampled_record():
+    """More carrier cycles than rows: 60 a row over 20,000 rows do not fit the fixed point, 20 do."""
+    elem = linear_array(4, 0.3e-3)
+    vox = column(step=1e-2, z0=0.1)
+    tx = (vox[None, :, 2] / C).astype(np.float32)
+    iq = random_iq((1, 4, 20_000, 2), seed=9)
+    for cycles, general in ((20, False), (60, True)):
+        kernel, db = run(iq, elem, vox, tx + np.float32(0.5), t0=0.5, fs=2e6, fd=2e6 * cycles)
+        assert (kernel == GENERAL) == general and db <= -100.0
