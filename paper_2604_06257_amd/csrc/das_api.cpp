@@ -217,12 +217,12 @@ int tile_points(const float* xyz, int64_t n, const char* spec, Tiling& out, std:
 
 namespace das {
 
-std::vector<int32_t> order_units(const Tiling& tl, const std::vector<int32_t>& item_off, int n_wt, int chunks) {
+std::vector<int32_t> order_units(const Tiling& tl, const std::vector<uint32_t>& item_off, int n_wt, int chunks) {
     const int per_tile = kWaves / n_wt;
     const int64_t n = tl.n_tiles * per_tile;
     std::vector<int32_t> units;
     units.reserve((size_t)(n * chunks));
-    auto cost = [&](int32_t u) { return item_off[(size_t)(u + 1) * n_wt] - item_off[(size_t)u * n_wt]; };
+    auto cost = [&](int32_t u) { return (int64_t)(item_off[((size_t)u + 1) * n_wt] - item_off[(size_t)u * n_wt]); };
     // columns = units of tiles sharing (x, y) tile coordinates; in row-major (y, x) order
     std::vector<int32_t> idx((size_t)n);
     std::iota(idx.begin(), idx.end(), 0);
@@ -497,7 +497,7 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
     for (int64_t k = 0; k < E; ++k)
         for (int a = 0; a < 3; ++a) elemd[4 * k + a] = (double)elem[3 * k + a];
     unsigned long long* counts = nullptr;
-    unsigned long long hc[4] = {0, 0, 0, 0};
+    unsigned long long hc[5] = {0, 0, 0, 0, 0};
     int2* win = nullptr;
     int32_t* n_items = nullptr;
     const int64_t n_wt = tl.n_tiles * das::kWaves;
@@ -538,32 +538,35 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
         d.groups = var.groups;
         const int chunks = (p->n_frames + var.fc - 1) / var.fc;
         das::choose_split(d, chunks, (int)std::min<unsigned long long>(hc[3], INT32_MAX), items_per_tile);
-        std::vector<int32_t> off((size_t)n_wt + 1, 0);
+        if (hc[4] > (unsigned long long)INT32_MAX) {  // the most (tile, element, transmit) windows that a plan holds
+            e = hipErrorInvalidValue;
+            goto hip_fail;
+        }
+        std::vector<uint32_t> off((size_t)n_wt + 1, 0);
         if (n_wt > 0 && !kp.wide) {
+            std::vector<int32_t> n((size_t)n_wt);
             if ((e = hipMalloc((void**)&n_items, n_wt * sizeof(int32_t))) != hipSuccess ||
-                (e = for_slabs([&](int t, int n) { return das::launch_items(d, t, n, win, nullptr, nullptr, n_items, s); })) !=
+                (e = for_slabs([&](int t, int k) { return das::launch_items(d, t, k, win, nullptr, nullptr, n_items, s); })) !=
                     hipSuccess ||
-                (e = hipMemcpyAsync(off.data() + 1, n_items, n_wt * sizeof(int32_t), hipMemcpyDeviceToHost, s)) !=
-                    hipSuccess ||
+                (e = hipMemcpyAsync(n.data(), n_items, n_wt * sizeof(int32_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
                 (e = hipStreamSynchronize(s)) != hipSuccess)
                 goto hip_fail;
-            int64_t sum = 0;
-            for (int64_t k = 1; k <= n_wt; ++k) {
-                sum += off[k];
-                off[k] = (int32_t)std::min<int64_t>(sum, INT32_MAX);
-            }
-            // more items than their offsets can count: the general kernel needs none
-            if (sum > (int64_t)INT32_MAX - das::kItemPad) {
-                kp.wide = 1;
-                std::fill(off.begin(), off.end(), 0);
+            uint64_t sum = 0;
+            for (int64_t k = 0; k < n_wt; ++k) {
+                sum += (uint64_t)n[(size_t)k] / 2;
+                if (n[(size_t)k] >= INT32_MAX - 1 || sum > UINT32_MAX) {
+                    e = hipErrorInvalidValue;
+                    goto hip_fail;
+                }
+                off[(size_t)k + 1] = (uint32_t)sum;
             }
         }
         std::vector<int4> order;
         for (const int32_t u : das::order_units(tl, off, d.n_wt, chunks)) {
             const int32_t wt = u / chunks * d.n_wt;
-            order.push_back(make_int4(wt, u % chunks, off[(size_t)wt], off[(size_t)wt + 1] - off[(size_t)wt]));
+            order.push_back(make_int4(wt, u % chunks, (int)off[(size_t)wt], (int)(off[(size_t)wt + 1] - off[(size_t)wt])));
         }
-        if ((e = hipMalloc((void**)&d.items, ((size_t)off.back() + das::kItemPad) * sizeof(int4))) != hipSuccess ||
+        if ((e = hipMalloc((void**)&d.items, (2 * (size_t)off.back() + das::kItemPad) * sizeof(int4))) != hipSuccess ||
             (e = upload(&d.item_off, off, s)) != hipSuccess || (e = upload(&d.wg_unit, order, s)) != hipSuccess)
             goto hip_fail;
         if (!kp.wide && (e = for_slabs([&](int t, int n) {

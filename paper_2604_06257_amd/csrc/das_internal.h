@@ -63,8 +63,8 @@ struct PlanDev {
     int32_t* slot_vox = nullptr;  // [n_slots]
     double* elemd = nullptr;   // [E][4] element coordinates (float32 inputs held in FP64), x y z 0
     int4* items = nullptr;     // per wave tile, its work items, element-major (and kItemPad more at the end)
-    int32_t* item_off = nullptr;  // [n_tiles * kWaves + 1] offsets into items
-    int4* wg_unit = nullptr;      // workgroup -> first wave tile, frame chunk, and that tile's first item and items
+    uint32_t* item_off = nullptr;  // [n_tiles * kWaves + 1] offsets into items, in pairs of them
+    int4* wg_unit = nullptr;      // workgroup -> first wave tile, frame chunk, and that tile's first pair of items and pairs
     int32_t fc = 0, pitch = 0, groups = 1;  // kernel variant: frames per workgroup, most rows per item + 1, element groups
     int32_t n_wt = kWaves, split = 1;       // wave tiles and element groups of a workgroup
     int32_t cap_rows = 0;                   // most rows of an item
@@ -75,7 +75,7 @@ struct PlanDev {
 // Workgroup -> unit order: each of the 8 XCDs gets a lateral region of tile columns (all depths), heaviest units
 // first inside a region, regions interleaved so that workgroup w runs on XCD w % 8.  A unit is a run of n_wt wave
 // tiles of one tile, times the frame chunk.
-std::vector<int32_t> order_units(const Tiling& tl, const std::vector<int32_t>& item_off, int n_wt, int chunks);
+std::vector<int32_t> order_units(const Tiling& tl, const std::vector<uint32_t>& item_off, int n_wt, int chunks);
 
 // Kernel variant for F frames, the largest tile window (rows), the tile count and the average number of
 // (transmit, element) items per tile.
@@ -95,11 +95,13 @@ int list_variants(int32_t* out, int capacity);
 // Computes per (wave tile, element, transmit) sample windows (first row, rows) of n tiles from tile0 on, and counts:
 // counts[0] = active (slot, e, t) triples (w > 0, inside the record);
 // counts[1] = processed triples (valid slots of tiles whose window is not
-// empty); counts[2] = longest tile window; counts[3] = longest wave window.
+// empty); counts[2] = longest tile window; counts[3] = longest wave window;
+// counts[4] = tile windows that are not empty.
 hipError_t launch_windows(const PlanDev& p, int tile0, int n, int2* win, unsigned long long* counts, hipStream_t s);
 
-// Items of those tiles' wave tiles (pieces of at most cap_rows rows): their numbers (items = null) or the items at off.
-hipError_t launch_items(const PlanDev& p, int tile0, int n, const int2* win, const int32_t* off, int4* items,
+// Items of those tiles' wave tiles (pieces of at most cap_rows rows): their numbers, even and at most INT32_MAX - 1 (items =
+// null), or the items at off (in pairs).
+hipError_t launch_items(const PlanDev& p, int tile0, int n, const int2* win, const uint32_t* off, int4* items,
                         int32_t* n_items, hipStream_t s);
 
 // Raises the dynamic LDS limit of the plan's kernels (all IQ types).

@@ -162,6 +162,7 @@ __global__ __launch_bounds__(kSlots) void window_stats_kernel(PlanDev p, int til
     __syncthreads();
     if (threadIdx.x == 0) {
         atomicAdd(&counts[1], s_n * (unsigned long long)s_valid);
+        atomicAdd(&counts[4], s_n);
         atomicMax(&counts[2], (unsigned long long)s_max);
     }
 }
@@ -169,11 +170,12 @@ __global__ __launch_bounds__(kSlots) void window_stats_kernel(PlanDev p, int til
 // Items of each wave tile: its non-empty windows cut into pieces of at most `cap` rows, element-major.  Without
 // `items`, only their number; one wave per wave tile.
 __global__ __launch_bounds__(kLanes) void items_kernel(das_kparams kp, int tile0, const int2* __restrict__ win,
-                                                       int cap, const int32_t* __restrict__ off,
+                                                       int cap, const uint32_t* __restrict__ off,
                                                        int4* __restrict__ items, int32_t* __restrict__ n_items) {
     const int wi = tile0 * kWaves + blockIdx.x, lane = threadIdx.x, T = kp.T, E = kp.E, n = E * T;
     const int2* const w = win + (int64_t)blockIdx.x * n;
-    int64_t at = items ? off[wi] : 0;
+    const int64_t first = items ? 2 * (int64_t)off[wi] : 0;
+    int64_t at = first;
     for (int i0 = 0; i0 < n; i0 += kLanes) {
         const int i = i0 + lane;
         const int2 x = i < n ? w[i] : make_int2(0, 0);
@@ -193,9 +195,9 @@ __global__ __launch_bounds__(kLanes) void items_kernel(das_kparams kp, int tile0
     }
     if (!items && lane == 0) n_items[wi] = (int32_t)min(at + (at & 1), (int64_t)INT_MAX - 1);
     // an even number of items: the last may have no rows
-    if (items && lane == 0 && ((at - off[wi]) & 1)) items[at] = make_int4(0, 0, 0, items[at - 1].w);
+    if (items && lane == 0 && ((at - first) & 1)) items[at] = make_int4(0, 0, 0, items[at - 1].w);
     // what a wave reads ahead past the last item loads nothing (no rows)
-    if (items && wi == kp.n_tiles * kWaves - 1 && lane < kItemPad) items[off[wi + 1] + lane] = make_int4(0, 0, 0, 0);
+    if (items && wi == kp.n_tiles * kWaves - 1 && lane < kItemPad) items[2 * (int64_t)off[wi + 1] + lane] = make_int4(0, 0, 0, 0);
 }
 
 hipError_t launch_windows(const PlanDev& p, int tile0, int n, int2* win, unsigned long long* counts, hipStream_t s) {
@@ -205,7 +207,7 @@ hipError_t launch_windows(const PlanDev& p, int tile0, int n, int2* win, unsigne
     return hipGetLastError();
 }
 
-hipError_t launch_items(const PlanDev& p, int tile0, int n, const int2* win, const int32_t* off, int4* items,
+hipError_t launch_items(const PlanDev& p, int tile0, int n, const int2* win, const uint32_t* off, int4* items,
                         int32_t* n_items, hipStream_t s) {
     hipLaunchKernelGGL(items_kernel, dim3(n * kWaves), dim3(kLanes), 0, s, p.kp, tile0, win, p.cap_rows, off, items,
                        n_items);
@@ -316,14 +318,15 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
         acc_i[f] = 0.0f;
     }
     // this group's share of the wave tile's items
-    int first = unit.z, n_items = unit.w;
+    uint32_t first = (uint32_t)unit.z;
+    int pairs = unit.w;
     if (lg_wt) {
         first = p.item_off[wi];
-        n_items = p.item_off[wi + 1] - first;
+        pairs = (int)(p.item_off[wi + 1] - first);
     }
-    const int pairs = n_items >> 1, share = pairs >> lg_groups, left = pairs & (groups - 1);
-    const int k0 = 2 * (share * grp + min(grp, left)), k1 = k0 + 2 * (share + (grp < left ? 1 : 0));
-    const auto* next = constant(reinterpret_cast<const uint64_t*>(p.items + first + k0));
+    const int share = pairs >> lg_groups, left = pairs & (groups - 1);
+    const int k0 = share * grp + min(grp, left), k1 = k0 + share + (grp < left ? 1 : 0);
+    const auto* next = constant(reinterpret_cast<const uint64_t*>(p.items + 2 * (size_t)(first + (uint32_t)k0)));
     const auto* const elem = constant(p.elemd);
 
     const int rl = lane / LPR, fg = lane % LPR;  // this lane's row and frame group of a load
@@ -522,7 +525,7 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
             nx = af;
             af = far;
         };
-        for (int k = k0; k < k1; k += 2) {
+        for (int k = k0; k < k1; ++k) {
             step(ca, cb, ea, eb, txa, txb);
             step(cb, ca, eb, ea, txb, txa);
         }

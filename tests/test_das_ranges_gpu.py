@@ -106,3 +106,31 @@ def test_high_carrier_in_a_slowly_sampled_record():
     for cycles, general in ((20, False), (60, True)):
         kernel, db = run(iq, elem, vox, tx + np.float32(0.5), t0=0.5, fs=2e6, fd=2e6 * cycles)
         assert (kernel == GENERAL) == general and db <= -100.0
+
+
+def test_item_lists_beyond_32_bits_keep_the_staged_kernel():
+    """2.4e9 work items (39 GB): 2,344 wave tiles that see every one of 16,384 x 64 (element, transmit) pairs."""
+    T, E, S, V = 64, 16_384, 64, 150_000
+    g = torch.Generator(device="cuda").manual_seed(5)
+    elem = torch.rand((E, 3), generator=g, device="cuda") * 1e-3
+    elem[:, 2] = 0
+    vox = torch.rand((V, 3), generator=g, device="cuda") * 1e-3 + torch.tensor([0.0, 0.0, 1e-3], device="cuda")
+    tx = (torch.rand((T, 1), generator=g, device="cuda") * 1e-7 + vox[None, :, 2] / C).float()
+    iq = torch.randn((T, E, S, 1, 2), generator=g, device="cuda").half()
+    p = das.Params(T, E, S, 1, V, C, FS, FD, 0.0, 0.0, 0.5)
+    with das.Plan(p, elem, vox, tx) as plan:
+        info = plan.info()
+        y = plan.execute(iq).to(torch.complex128)[:, 0]
+    assert info["kernel"] != GENERAL and info["active_triples"] == V * E * T
+    idx = torch.randperm(V, generator=g, device="cuda")[:192].sort().values
+    ref = torch.zeros(192, dtype=torch.complex128, device="cuda")
+    q = torch.view_as_complex(iq[:, :, :, 0].double())
+    for n, v in enumerate(idx):
+        tau = tx[:, v].double()[:, None] + (vox[v].double() - elem.double()).norm(dim=1)[None] / C
+        u = tau * FS
+        i0 = u.floor().long()[..., None]
+        beta = u - u.floor()
+        s = torch.lerp(q.gather(2, i0)[..., 0], q.gather(2, i0 + 1)[..., 0], beta.to(torch.complex128))
+        ref[n] = (s * torch.polar(torch.ones_like(tau), 2 * np.pi * FD * tau)).sum()
+    # 65,536 float32 additions a group, sums growing with the root of their number: 2^-24 * 256 = -96 dB
+    assert oracle.nrmse_db(y[idx].cpu().numpy(), ref.cpu().numpy()) <= -90.0
