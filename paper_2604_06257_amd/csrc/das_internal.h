@@ -41,8 +41,9 @@ constexpr int lds_row_bytes(int fc) { return fc <= 2 ? 8 * fc : 8 * fc + 16; }
 //         and the window's rows (bits 24-31)
 //   z     the window's first row + row_fix (the high word of a fixed-point sample coordinate in that row);
 //         a window that begins at row -1 loads from row 0
-//   w     element << 12 | transmit
-constexpr int kMaxElem = 1 << 20, kMaxTx = 1 << 12, kMaxRows = 254;
+//   w     element << kTxBits | transmit (a split that depends on the plan took two more scalar registers and 2 % of the time
+//         of three transmits apart at 96^3 x 1024 elements, 1009 -> 1034 us)
+constexpr int kTxBits = 14, kMaxTx = 1 << kTxBits, kMaxElem = 1 << (32 - kTxBits), kMaxRows = 254;
 constexpr int kItemPad = 4;  // items past the end that a wave may read ahead
 #ifdef __HIPCC__
 __host__ __device__
@@ -51,7 +52,7 @@ inline int4 pack_item(int e, int t, int row, int rows, int E, int S, int F, int 
     const int from = row < 0 ? 0 : row, end = row + rows + 1 < S ? row + rows + 1 : S, loaded = end - from;
     const int64_t off = (((int64_t)t * E + e) * S + from) * F;
     return int4{(int)(uint32_t)off, (int)((uint32_t)(off >> 32) | (uint32_t)loaded << 16 | (uint32_t)rows << 24),
-                row + row_fix, (int)((uint32_t)e << 12 | (uint32_t)t)};
+                row + row_fix, (int)((uint32_t)e << kTxBits | (uint32_t)t)};
 }
 
 struct PlanDev {

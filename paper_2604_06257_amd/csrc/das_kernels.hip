@@ -354,8 +354,8 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
             return (int)r;
         }
         __device__ int loaded() const { return (int)__builtin_amdgcn_ubfe((uint32_t)(at >> 32), 16, 8); }
-        __device__ int e() const { return (int)(et >> 12); }
-        __device__ int t() const { return (int)(et & 4095); }
+        __device__ int e() const { return (int)(et >> kTxBits); }
+        __device__ int t() const { return (int)(et & (kMaxTx - 1)); }
     };
     auto item = [&] {
         const uint64_t a = next[0], b = next[1];
@@ -431,7 +431,7 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
     auto coords = [&](const Item& it) {
         // (a 32-bit offset that the compiler cannot see through goes into the load; it would add 64 bits otherwise: three
         // transmits apart at 96^3 x 1024 elements 1079 -> 1049 us, scalar instructions bounding them)
-        uint32_t off = it.et >> 12 << 5;
+        uint32_t off = it.et >> kTxBits << 5;
         asm("" : "+s"(off));
         const auto* e = (const __attribute__((address_space(4))) f64x2*)((const __attribute__((address_space(4))) char*)elem + off);
         const f64x2 xy = e[0];

@@ -134,3 +134,13 @@ def test_item_lists_beyond_32_bits_keep_the_staged_kernel():
         ref[n] = (s * torch.polar(torch.ones_like(tau), 2 * np.pi * FD * tau)).sum()
     # 65,536 float32 additions a group, sums growing with the root of their number: 2^-24 * 256 = -96 dB
     assert oracle.nrmse_db(y[idx].cpu().numpy(), ref.cpu().numpy()) <= -90.0
+
+
+@pytest.mark.parametrize("T,E", [(4096, 3), (4097, 3), (16_384, 2), (1, 5000), (3, 16_385)])
+def test_many_transmits_or_elements_keep_the_staged_kernel(T, E):
+    elem = np.zeros((E, 3), np.float32)
+    elem[:, 0] = np.linspace(-1e-3, 1e-3, E)
+    vox = column(70)
+    tx = (vox[None, :, 2] / C + 1e-7 * np.arange(T)[:, None] / T).astype(np.float32)
+    kernel, db = run(random_iq((T, E, 220, 1), seed=T), elem, vox, tx)
+    assert kernel != GENERAL and db <= -100.0
