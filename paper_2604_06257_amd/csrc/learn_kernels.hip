@@ -13,6 +13,7 @@
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
 
+#include <algorithm>
 #include <atomic>
 #include <cstdint>
 #include <type_traits>
@@ -285,6 +286,8 @@ struct WgradShape {
     int nyb, nwb;      // blocks along H and W
     int parts;
     int lds;           // bytes
+    int64_t slice, row, col;  // voxels from a slice, a row, a column to the next, and the taps' (kPerm)
+    int tap_slice, tap_row, tap_col;
 };
 
 // KiB of LDS that n voxels take, in whole loads of a wave.
@@ -299,8 +302,9 @@ __device__ __forceinline__ bf16x8 tr_read(uint32_t at) {
 __device__ __attribute__((aligned(16))) const uint32_t kZeros[4] = {0, 0, 0, 0};
 
 // k64: a block's rows span 2 GiB or more: per-lane 64-bit addresses (of a constant zero where a lane is out of range)
-// instead of 32-bit offsets into a buffer resource.
-template <bool k64>
+// instead of 32-bit offsets into a buffer resource.  kPerm: `vol` is the volume with its axes in another order (sh says how;
+// a form of its own, since strides held in registers cost the plain one up to a third).
+template <bool k64, bool kPerm>
 __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __restrict__ in, int in_stride, int in_coff,
                                                               const uint16_t* __restrict__ dy, int dy_stride,
                                                               int dy_coff, float* __restrict__ part,
@@ -328,20 +332,22 @@ __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __
     const char *xbase = nullptr, *ybase = nullptr;
     auto block = [&](int h0, int w0) {
         const int hx = max(h0 - 1, 0);
-        xbase = reinterpret_cast<const char*>(in + in_coff + (int64_t)hx * vol.W * in_stride);
-        ybase = reinterpret_cast<const char*>(dy + dy_coff + n0 + (int64_t)h0 * vol.W * dy_stride);
+        xbase = reinterpret_cast<const char*>(in + in_coff + (kPerm ? hx * sh.row : (int64_t)hx * vol.W) * in_stride);
+        ybase = reinterpret_cast<const char*>(dy + dy_coff + n0 + (kPerm ? h0 * sh.row : (int64_t)h0 * vol.W) * dy_stride);
 #pragma unroll
         for (int k = 0; k < kWgX; ++k) {
             const int v = ((wave + kWgWaves * k) * 64 + lane) >> 1, r = v / pitch, h = h0 - 1 + r, w = w0 + (v - r * pitch);
             const bool ok = r < sh.bh + 2 && v - r * pitch < sh.wb && c0 + 8 * half < Cin && (unsigned)h < (unsigned)vol.H &&
                             w < vol.W;
-            xo[k] = ok ? (((off_t)(h - hx) * vol.W + w) * in_stride + c0 + 8 * half) * 2 : kOut;
+            if constexpr (kPerm) xo[k] = ok ? (((off_t)(h - hx) * (off_t)sh.row + w * (off_t)sh.col) * in_stride + c0 + 8 * half) * 2 : kOut;
+            else xo[k] = ok ? (((off_t)(h - hx) * vol.W + w) * in_stride + c0 + 8 * half) * 2 : kOut;
         }
 #pragma unroll
         for (int k = 0; k < kWgY; ++k) {
             const int v = ((wave + kWgWaves * k) * 64 + lane) >> 1, r = v / pitch, h = h0 + r, w = w0 - 1 + (v - r * pitch);
             const bool ok = r < sh.bh && h < vol.H && (unsigned)w < (unsigned)vol.W;
-            yo[k] = ok ? (((off_t)r * vol.W + w) * dy_stride + 8 * half) * 2 : kOut;
+            if constexpr (kPerm) yo[k] = ok ? (((off_t)r * (off_t)sh.row + w * (off_t)sh.col) * dy_stride + 8 * half) * 2 : kOut;
+            else yo[k] = ok ? (((off_t)r * vol.W + w) * dy_stride + 8 * half) * 2 : kOut;
         }
     };
     // One KiB: 16 bytes per lane, to consecutive LDS places from `at` on (wave-uniform).
@@ -356,7 +362,8 @@ __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __
                          : "memory");
         }
     };
-    const int64_t xslice = (int64_t)vol.H * vol.W * in_stride * 2, yslice = (int64_t)vol.H * vol.W * dy_stride * 2;
+    const int64_t xslice = (kPerm ? sh.slice : (int64_t)vol.H * vol.W) * in_stride * 2,
+                  yslice = (kPerm ? sh.slice : (int64_t)vol.H * vol.W) * dy_stride * 2;
     auto load_x = [&](int z) {
         const bool none = (unsigned)z >= (unsigned)vol.D;
         const char* const src = xbase + (none ? 0 : z) * xslice;
@@ -461,8 +468,10 @@ __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __
 #pragma unroll
                     for (int r = 0; r < 4; ++r) part_db[(int64_t)my_part * Cout + n0 + 4 * (lane >> 4) + r] = y[r];
             } else if (c < Cin) {
+                const int i = upper * 5 + t / 3;
+                const int tap = kPerm ? i / 3 * sh.tap_slice + i % 3 * sh.tap_row + t % 3 * sh.tap_col : upper * 15 + t;
 #pragma unroll
-                for (int r = 0; r < 4; ++r) pb[((int64_t)r * 27 + upper * 15 + t) * Cin] = y[r];
+                for (int r = 0; r < 4; ++r) pb[((int64_t)r * 27 + tap) * Cin] = y[r];
             }
         }
     }
@@ -1284,7 +1293,7 @@ constexpr int kLdsBytes = 160 * 1024;
 
 // Raises a kernel's dynamic LDS limit on the current device, once per device (`done`: a bit each; setting it twice does
 // no harm).  A launch past the limit fails by itself.
-std::atomic<uint64_t> g_wgrad_devices[2];
+std::atomic<uint64_t> g_wgrad_devices[4];
 void allow_lds(const void* kernel, std::atomic<uint64_t>& done) {
     int dev = 0;
     if (hipGetDevice(&dev) != hipSuccess) return;
@@ -1300,9 +1309,9 @@ void allow_lds(const void* kernel, std::atomic<uint64_t>& done) {
 // (480 cycles per 32 voxels) and about 1000 cycles more (two workgroups on a CU hide half of that); within what the
 // waves' loads and their share of the LDS hold.  (32 -> 32 channels at 48^3: 18.9 us as two workgroups per CU, 16.3 us
 // as one of 12-row blocks; 112 -> 48 at 24^3: 16.6 and 15.0 us.)
-learn::WgradShape wgrad_shape(const learn::Vol& vol, int pairs, int nparts) {
+learn::WgradShape wgrad_shape(const learn::Vol& vol, int pairs, int nparts, double& best_cost) {
     learn::WgradShape best{};
-    double best_cost = 0.0;
+    best_cost = 0.0;
     const int nwb = (vol.W + 127) / 128, wb = (vol.W + nwb - 1) / nwb, pitch = wb + 2;
     const int red = 2 * learn::kWgPhase * learn::kWgSplit * 1024;  // the waves' sums
     for (int per_cu = 1; per_cu <= 2; ++per_cu) {
@@ -1323,7 +1332,7 @@ learn::WgradShape wgrad_shape(const learn::Vol& vol, int pairs, int nparts) {
             const double cost = (double)((steps + p - 1) / p) * (rounds * 480.0 * per_cu + 1000.0);
             if (best.bh == 0 || cost < best_cost) {
                 best_cost = cost;
-                best = learn::WgradShape{bh, wb, nyb, nwb, (int)p, lds};
+                best = learn::WgradShape{bh, wb, nyb, nwb, (int)p, lds, 0, 0, 0, 0, 0, 0};
             }
         }
     }
@@ -1333,11 +1342,35 @@ learn::WgradShape wgrad_shape(const learn::Vol& vol, int pairs, int nparts) {
 int launch_wgrad(int nparts, hipStream_t s, const uint16_t* in, int in_stride, int in_coff, const uint16_t* dy,
                  int dy_stride, int dy_coff, float* part, float* part_db, learn::Vol vol, int cin, int cout) {
     const int pairs = cout / 16 * ((cin + 15) / 16);
-    const learn::WgradShape sh = wgrad_shape(vol, pairs, nparts);
-    const int stride = in_stride > dy_stride ? in_stride : dy_stride;
-    const bool big = (int64_t)(sh.bh + 2) * vol.W * stride * 2 >= (int64_t)1 << 31;
-    const auto kernel = big ? learn::wgrad_kernel<true> : learn::wgrad_kernel<false>;
-    allow_lds((const void*)kernel, g_wgrad_devices[big]);
+    double cost = 0.0;
+    learn::WgradShape sh = wgrad_shape(vol, pairs, nparts, cost);
+    // A volume of few short rows in few parts is a chain of short steps, or of padding; with its axes in another order it may
+    // be few long ones (16 -> 16 channels in one part: 64 x 3 x 3 52 and 12, 31 x 48 x 1 38 and 17 us).  Voxels then come
+    // one by one from afar, so the other order has to promise a third less (and is not looked for where no order can).
+    bool perm = false;
+    const int n[3] = {vol.D, vol.H, vol.W}, tap[3] = {9, 3, 1}, order[5][3] = {{1, 0, 2}, {0, 2, 1}, {2, 1, 0}, {1, 2, 0}, {2, 0, 1}};
+    const int64_t far[3] = {(int64_t)vol.H * vol.W, vol.W, 1};
+    double least = cost / 1.5;
+    const double voxels = (double)vol.D * vol.H * vol.W / (pairs < 256 ? std::min(256 / pairs, nparts) : 1);
+    for (const auto& o : order) {
+        if (least < voxels / (32 * learn::kWgSplit) * 480.0 + 1480.0) break;
+        double c = 0.0;
+        const learn::Vol v{n[o[0]], n[o[1]], n[o[2]]};
+        learn::WgradShape p = wgrad_shape(v, pairs, nparts, c);
+        if (c >= least) continue;
+        least = c;
+        sh = p;
+        sh.slice = far[o[0]], sh.row = far[o[1]], sh.col = far[o[2]];
+        sh.tap_slice = tap[o[0]], sh.tap_row = tap[o[1]], sh.tap_col = tap[o[2]];
+        vol = v;
+        perm = true;
+    }
+    const int64_t stride = in_stride > dy_stride ? in_stride : dy_stride;
+    const int64_t span = perm ? (sh.bh + 2) * sh.row + vol.W * sh.col : (int64_t)(sh.bh + 2) * vol.W;
+    const bool big = span * stride * 2 >= (int64_t)1 << 31;
+    const auto kernel = big ? perm ? learn::wgrad_kernel<true, true> : learn::wgrad_kernel<true, false>
+                            : perm ? learn::wgrad_kernel<false, true> : learn::wgrad_kernel<false, false>;
+    allow_lds((const void*)kernel, g_wgrad_devices[2 * big + perm]);
     hipLaunchKernelGGL(kernel, dim3((sh.parts * pairs + 7) / 8 * 8), dim3(learn::kWgThreads), sh.lds, s, in, in_stride,
                        in_coff, dy, dy_stride, dy_coff, part, part_db, vol, cin, cout, sh);
     return sh.parts;
