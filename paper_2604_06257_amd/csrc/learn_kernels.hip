@@ -1427,7 +1427,9 @@ bool launch_brick(const ConvArgs& a, hipStream_t s) {
 // float32 output, every voxel of a halo within 2 GiB of its first (which may lie a slice, a row and a voxel before the
 // tensor) and rows of less than 2^24 channels (32-bit offsets), weights and halo within a CU's LDS (up to 128 channels).
 // Rows up to 8 voxels fill at most half of its 16: there it takes only what gains all the same, one held chunk or 64
-// channels and more (8^3: 64 -> 64 channels 10.0 us by conv3d_kernel and 7.4 us by this, 32 -> 32 5.3 and 5.5 us).
+// channels and more (8^3: 64 -> 64 channels 10.0 us by conv3d_kernel and 7.4 us by this, 32 -> 32 5.3 and 5.5 us); of these
+// not what conv3d_kernel walks 4 slices at a time, except 64 and 128 channels (96 x 96 x 3: 64 -> 32 0.85 of its time, 96 -> 32
+// 1.10, 120 -> 32 1.53; at 8 columns 0.87, 1.05, 1.07).
 // One chunk of 8 or 16 channels: held in registers, 4 waves, two buffers (16 -> 16 at 96^3: 15.4 us; 18.0 us with the
 // weights in LDS).  32-channel chunks: one buffer where two workgroups then fit on a CU (32 -> 32 at 48^3: 9.7 us, with two
 // buffers 11.4 us), else two if they fit (64 -> 64 at 96 x 96 x 8: 39 and 37 us).  Several chunks of 8 or 16: two buffers,
@@ -1440,7 +1442,7 @@ bool try_brick(const ConvArgs& a, hipStream_t s) {
     if (!al(a.out, a.out_f32 ? 16 : 8) || a.out_stride % 4 || a.out_coff % 4 || (a.mask && a.out_f32) ||
         (a.mask && (!al(a.mask, 8) || a.mask_stride % 4 || a.mask_coff % 4 || a.mask_stride >= 1 << 24)) ||
         a.out_stride >= 1 << 24 || halo > (int64_t)1 << 31 ||
-        (a.vol.W <= 8 && !held && a.cin < 64))
+        (a.vol.W <= 8 && !held && (a.cin < 64 || (a.cin % 64 && pick_conv_shape(a.cout / 16, a.vol).mt == 4))))
         return false;
     const learn::BrickShape rows8 = brick_shape(a.vol, 8);
     const bool tall = (int64_t)rows8.nx * rows8.ny * rows8.nz * (a.cout / 16) >= 192;
