@@ -691,6 +691,8 @@ hipError_t launch_das_per_tx(const PlanDev& p, const void* iq, int dtype, void* 
     X(2, 257, 1) X(2, 513, 1) X(2, 1025, 1) X(1, 65, 1) X(1, 129, 1) X(1, 257, 1) X(1, 513, 1) X(1, 1025, 1) X(1, 2049, 1) \
     X(1, 65, 4) X(1, 129, 4) X(1, 257, 4) X(2, 129, 4) X(2, 257, 4) X(4, 65, 4) X(4, 129, 4) X(8, 65, 2) X(8, 65, 4) X(8, 33, 2) X(8, 129, 2) X(16, 65, 4) X(4, 65, 2) \
     X(1, 65, 2) X(1, 129, 2) X(1, 257, 2) X(2, 129, 2) X(2, 257, 2) X(4, 129, 2) X(8, 129, 4)                  \
+    X(8, 257, 2) X(8, 257, 4) X(4, 257, 2) X(4, 257, 4) X(4, 513, 2) X(4, 513, 4) X(2, 513, 2) X(2, 513, 4) X(2, 1025, 2) \
+    X(2, 1025, 4) X(1, 513, 2) X(1, 513, 4) X(1, 1025, 2) X(1, 1025, 4) X(1, 2049, 2) X(1, 2049, 4) \
     X(1, 0, 1) X(1, 0, 2) X(1, 0, 4) X(2, 0, 1) X(2, 0, 2) X(2, 0, 4)
 
 // Variant choice, from the frame count, the longest tile window, the tile count and the items per tile:
