@@ -160,7 +160,8 @@ typedef struct das_plan_info {
     int32_t kernel_fc;         /* kernel variant: frames per workgroup (0, 0, 0:
                                   the general kernel, far slower),             */
     int32_t kernel_pitch;      /*   most window rows per work item + 1 (0: only
-                                      the LDS bounds them),                    */
+                                      the LDS bounds them; -1: windows of many
+                                      rows, lanes gather their samples),       */
     int32_t kernel_groups;     /*   element groups per tile, at least (a plan
                                       may split its waves' items further)      */
 } das_plan_info;

@@ -497,7 +497,7 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
     for (int64_t k = 0; k < E; ++k)
         for (int a = 0; a < 3; ++a) elemd[4 * k + a] = (double)elem[3 * k + a];
     unsigned long long* counts = nullptr;
-    unsigned long long hc[5] = {0, 0, 0, 0, 0};
+    unsigned long long hc[7] = {0, 0, 0, 0, 0, 0, 0};
     int2* win = nullptr;
     int32_t* n_items = nullptr;
     const int64_t n_wt = tl.n_tiles * das::kWaves;
@@ -536,7 +536,8 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
         d.fc = var.fc;
         d.pitch = var.pitch;
         d.groups = var.groups;
-        const int chunks = (p->n_frames + var.fc - 1) / var.fc;
+        das::choose_gather(d, hc[6] > 0 ? (double)hc[5] / (double)hc[6] : 0.0);
+        const int chunks = (p->n_frames + d.fc - 1) / d.fc;
         das::choose_split(d, chunks, (int)std::min<unsigned long long>(hc[3], INT32_MAX), items_per_tile);
         if (hc[4] > (unsigned long long)INT32_MAX) {  // the most (tile, element, transmit) windows that a plan holds
             e = hipErrorInvalidValue;
@@ -679,7 +680,7 @@ int das_plan_query(const das_plan* plan, das_plan_info* info) {
     info->max_window = plan->max_window;
     const bool general = plan->dev.kp.wide != 0;
     info->kernel_fc = general ? 0 : plan->dev.fc;
-    info->kernel_pitch = general ? 0 : plan->dev.pitch;
+    info->kernel_pitch = general ? 0 : plan->dev.cap_rows == das::kGather ? -1 : plan->dev.pitch;
     info->kernel_groups = general ? 0 : plan->dev.groups;
     return DAS_OK;
 }

@@ -44,6 +44,7 @@ constexpr int lds_row_bytes(int fc) { return fc <= 2 ? 8 * fc : 8 * fc + 16; }
 //   w     element << kTxBits | transmit (a split that depends on the plan took two more scalar registers and 2 % of the time
 //         of three transmits apart at 96^3 x 1024 elements, 1009 -> 1034 us)
 constexpr int kTxBits = 14, kMaxTx = 1 << kTxBits, kMaxElem = 1 << (32 - kTxBits), kMaxRows = 254;
+constexpr int kGather = 1 << 30;  // cap_rows of plans whose lanes gather their samples: whole windows, rows left out
 constexpr int kItemPad = 4;  // items past the end that a wave may read ahead
 #ifdef __HIPCC__
 __host__ __device__
@@ -69,6 +70,7 @@ struct PlanDev {
     int32_t fc = 0, pitch = 0, groups = 1;  // kernel variant: frames per workgroup, most rows per item + 1, element groups
     int32_t n_wt = kWaves, split = 1;       // wave tiles and element groups of a workgroup
     int32_t cap_rows = 0;                   // most rows of an item
+    bool per_tx = false;                    // per-transmit output is served
     int64_t launch_units = 0;               // most workgroups of a launch
     int64_t n_vox = 0;                      // voxels (per-transmit output stride: n_vox * F)
 };
@@ -85,6 +87,10 @@ struct Variant {
 };
 Variant choose_variant(int frames, int max_window, int64_t n_tiles, double items_per_tile);
 
+// Sets what the plan's variant says of its kernel: per_tx, and for windows of many rows on average that lanes gather their
+// samples (cap_rows = kGather, possibly more frames per workgroup).
+void choose_gather(PlanDev& p, double mean_rows);
+
 // Sets the plan's workgroup shape (n_wt, split) and item length (cap_rows) for its variant, the frame chunks, the
 // longest wave window and the items per tile.
 void choose_split(PlanDev& p, int chunks, int max_wave_window, double items_per_tile);
@@ -97,7 +103,8 @@ int list_variants(int32_t* out, int capacity);
 // counts[0] = active (slot, e, t) triples (w > 0, inside the record);
 // counts[1] = processed triples (valid slots of tiles whose window is not
 // empty); counts[2] = longest tile window; counts[3] = longest wave window;
-// counts[4] = tile windows that are not empty.
+// counts[4] = tile windows that are not empty; counts[5], counts[6] = rows and
+// number of the wave windows that are not empty.
 hipError_t launch_windows(const PlanDev& p, int tile0, int n, int2* win, unsigned long long* counts, hipStream_t s);
 
 // Items of those tiles' wave tiles (pieces of at most cap_rows rows): their numbers, even and at most INT32_MAX - 1 (items =

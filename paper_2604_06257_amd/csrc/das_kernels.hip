@@ -93,8 +93,8 @@ __global__ __launch_bounds__(kSlots) void window_kernel(PlanDev p, int tile0, in
     const das_lane vl = das_lane_setup(p.vx[slot], p.vy[slot], p.vz[slot], kp);
     const int n = kp.E * kp.T;
     int2* const dst = win + (int64_t)(wi - tile0 * kWaves) * n;
-    unsigned long long active = 0;
-    int i = 0, longest = 0;
+    unsigned long long active = 0, rows = 0;
+    int i = 0, longest = 0, used = 0;
     int2 mine = make_int2(0, 0);
     for (int e = 0; e < kp.E; ++e) {
         const das_rx rx = das_rx_setup(vl, p.elemd[4 * e], p.elemd[4 * e + 1], p.elemd[4 * e + 2], kp);
@@ -116,6 +116,8 @@ __global__ __launch_bounds__(kSlots) void window_kernel(PlanDev p, int tile0, in
                 w = make_int2(lo, hi - lo + 1);
                 active += (unsigned long long)__popcll(ball);
                 longest = max(longest, w.y);
+                rows += (unsigned)w.y;
+                ++used;
             }
             if ((i & 63) == lane) mine = w;
             if ((i & 63) == 63) dst[i - 63 + lane] = mine;
@@ -125,6 +127,8 @@ __global__ __launch_bounds__(kSlots) void window_kernel(PlanDev p, int tile0, in
     if (lane == 0) {
         atomicAdd(&counts[0], active);
         atomicMax(&counts[3], (unsigned long long)longest);
+        atomicAdd(&counts[5], rows);
+        atomicAdd(&counts[6], (unsigned long long)used);
     }
 }
 
@@ -179,7 +183,7 @@ __global__ __launch_bounds__(kLanes) void items_kernel(das_kparams kp, int tile0
     for (int i0 = 0; i0 < n; i0 += kLanes) {
         const int i = i0 + lane;
         const int2 x = i < n ? w[i] : make_int2(0, 0);
-        const int pieces = (x.y + cap - 1) / cap;
+        const int pieces = cap == kGather ? (x.y > 0 ? 1 : 0) : (x.y + cap - 1) / cap;
         int before = pieces;  // inclusive scan
         for (int o = 1; o < kLanes; o <<= 1) {
             const int y = __shfl_up(before, o);
@@ -188,8 +192,12 @@ __global__ __launch_bounds__(kLanes) void items_kernel(das_kparams kp, int tile0
         if (items) {
             const int e = i / T, t = i - e * T;
             int4* dst = items + at + (before - pieces);
-            for (int r = 0; r < x.y; r += cap)
-                *dst++ = pack_item(e, t, x.x + r, min(cap, x.y - r), E, kp.S, kp.F, kp.row_fix);
+            if (cap == kGather) {
+                if (x.y > 0) *dst = pack_item(e, t, 0, 1, E, kp.S, kp.F, kp.row_fix);
+            } else {
+                for (int r = 0; r < x.y; r += cap)
+                    *dst++ = pack_item(e, t, x.x + r, min(cap, x.y - r), E, kp.S, kp.F, kp.row_fix);
+            }
         }
         at += __shfl(before, kLanes - 1);
     }
@@ -247,6 +255,7 @@ typedef __attribute__((address_space(3))) char lds_char;
 constexpr int das_waves(int fc, int ntx, bool planar) {
     return fc >= 16 ? 4 : fc >= 8 ? 6 : ((fc == 2 && ntx > 1) || !planar) ? 7 : 8;
 }
+constexpr int das_gather_waves(int fc, int ntx) { return fc >= 8 ? (ntx > 1 ? 4 : 5) : 8; }
 constexpr int kMaxThreads = 1024;
 
 // Sums the groups' accumulators in a fixed order, ((g0 + g1) + g2) + ..., and writes them.  With several groups all of
@@ -534,6 +543,87 @@ void das_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out
                              tx_stride, out);
 }
 
+// Long windows: a lane reads its own two rows of every item straight from the record, FC frames of each, with no LDS but for
+// the groups' sums.  choose_gather says when.
+// Bound by the cache's rate on 64 places at a time; the rows of an item are all asked for before the first is used, and many
+// waves hide the wait.
+template <int FC, int DT, int NTX>
+__global__ __launch_bounds__(kMaxThreads) __attribute__((amdgpu_waves_per_eu(das_gather_waves(FC, NTX), das_gather_waves(FC, NTX))))
+void das_gather_kernel(PlanDev p, const void* __restrict__ iq, float2* __restrict__ out, int lg_wt, int lg_halves, int lg_groups,
+                       int64_t tx_stride) {
+    constexpr int kEB = IQType<DT>::kBytes, FPT = FC < IQType<DT>::kVec ? FC : IQType<DT>::kVec;
+    using Raw = typename RawT<FPT * kEB>::type;
+    extern __shared__ __attribute__((aligned(16))) char lds[];
+    const das_kparams& kp = p.kp;
+    const int lane = threadIdx.x & 63;
+    const int wave = __builtin_amdgcn_readfirstlane((int)(threadIdx.x >> 6));
+    const int lg_cols = lg_wt + lg_halves, cols = 1 << lg_cols, groups = 1 << lg_groups;
+    const int col = wave & (cols - 1), grp = wave >> lg_cols;
+    const int4 unit = p.wg_unit[blockIdx.x];
+    const int wi = unit.x + (col & ((1 << lg_wt) - 1));
+    const int f0 = ((unit.y << lg_halves) + (col >> lg_wt)) * FC;
+    const int64_t slot = (int64_t)wi * kLanes + lane;
+    const int vox = p.slot_vox[slot];
+    const das_lane L = das_lane_setup(p.vx[slot], p.vy[slot], p.vz[slot], kp);
+    float acc_r[NTX * FC], acc_i[NTX * FC];
+#pragma unroll
+    for (int f = 0; f < NTX * FC; ++f) acc_r[f] = acc_i[f] = 0.0f;
+    const uint32_t first = p.item_off[wi];
+    const int pairs = (int)(p.item_off[wi + 1] - first), share = pairs >> lg_groups, left = pairs & (groups - 1);
+    const int k0 = share * grp + min(grp, left), k1 = k0 + share + (grp < left ? 1 : 0);
+    const auto* next = constant(reinterpret_cast<const uint64_t*>(p.items + 2 * (size_t)(first + (uint32_t)k0)));
+    const auto* const elem = constant(p.elemd);
+    const float* const txs = p.tx + (int64_t)wi * kp.T * kLanes + lane;
+    const int row_bytes = kp.F * kEB, rec_bytes = kp.S * row_bytes;
+    int last_e = -1;
+    das_rx rx;
+    for (int k = 2 * k0; k < 2 * k1; ++k) {
+        const uint64_t at = next[0];
+        const uint32_t et = (uint32_t)(next[1] >> 32);
+        next += 2;
+        const int e = (int)(et >> kTxBits), t = (int)(et & (kMaxTx - 1));
+        if (e != last_e) {
+            rx = das_rx_setup(L, elem[4 * e], elem[4 * e + 1], elem[4 * e + 2], kp);
+            last_e = e;
+        }
+        const das_coef c = das_tx_setup(rx, das_tx_const(txs[t * kLanes], kp.fix_t0, kp.fix_ph, kp), kp);
+        // (an item of no rows pads the list; a lane that has no part in the item reads zeros)
+        const bool on = das_active(rx, c, kp) & ((at >> 56) != 0);
+        const uint32_t off = on ? (uint32_t)((c.hi - kp.row_fix) * row_bytes + f0 * kEB) : 0x80000000u;
+        const __amdgpu_buffer_rsrc_t rs = __builtin_amdgcn_make_buffer_rsrc(
+            reinterpret_cast<void*>(reinterpret_cast<uint64_t>(iq) + at * kEB), (short)0, rec_bytes, 0x00020000);
+        auto load = [&](uint32_t o) {
+            if constexpr (sizeof(Raw) == 16) return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b128(rs, o, 0, 0));
+            else if constexpr (sizeof(Raw) == 8) return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b64(rs, o, 0, 0));
+            else return __builtin_bit_cast(Raw, __builtin_amdgcn_raw_buffer_load_b32(rs, o, 0, 0));
+        };
+        Raw q0[FC / FPT], q1[FC / FPT];
+#pragma unroll
+        for (int g = 0; g < FC / FPT; ++g) {
+            q0[g] = load(off + g * FPT * kEB);
+            q1[g] = load(off + g * FPT * kEB + (on ? row_bytes : 0));
+        }
+        auto mac = [&](int a0) {
+#pragma unroll
+            for (int f = 0; f < FC; ++f) {
+                const float2 a = decode<DT>(q0[f / FPT], f % FPT), b = decode<DT>(q1[f / FPT], f % FPT);
+                const float tr = fmaf(c.beta, b.x - a.x, a.x), ti = fmaf(c.beta, b.y - a.y, a.y);
+                acc_r[a0 + f] = fmaf(-c.ci, ti, fmaf(c.cr, tr, acc_r[a0 + f]));
+                acc_i[a0 + f] = fmaf(c.ci, tr, fmaf(c.cr, ti, acc_i[a0 + f]));
+            }
+        };
+        if constexpr (NTX == 1) {
+            mac(0);
+        } else {
+#pragma unroll
+            for (int j = 0; j < NTX; ++j)
+                if (t == j) mac(j * FC);
+        }
+    }
+    das_finish<NTX * FC, FC>(lds, acc_r, acc_i, col * kLanes + lane, cols * kLanes, grp, lg_groups, vox, f0, kp.F, kp.T,
+                             tx_stride, out);
+}
+
 // Any finite geometry: FP64 delays and phases, samples gathered from the record, every (element, transmit) visited.
 // Serves only plans whose delays or phases leave the fixed point's range or whose sizes do not fit an item.
 template <int DT>
@@ -574,6 +664,7 @@ __global__ __launch_bounds__(kSlots) void das_wide_kernel(PlanDev p, const void*
 
 // ---------------------------------------------------------------- launches
 constexpr int kPerTx = 4;  // transmits of per-transmit output (variants of at most 2 frames per workgroup)
+constexpr int kGatherFrames = 8;  // frames that gathering waves take of more than 8
 
 template <int FC, int DT>
 static int wave_bytes(const PlanDev& p) {
@@ -581,19 +672,9 @@ static int wave_bytes(const PlanDev& p) {
     return ((p.cap_rows + St::RPI) / St::RPI * St::RPI + 2) * St::PB;  // cap_rows + 1 rows in whole loads, two of zeros
 }
 
-template <int FC, int DT, int NTX, bool kOne, bool kPlanar>
-static hipError_t launch_k(const PlanDev& p, const void* iq, void* out, hipStream_t s) {
-    const int halves = p.fc / FC, nchunk = (p.kp.F + p.fc - 1) / p.fc, waves = p.n_wt * halves * p.split;
-    const int wb = wave_bytes<FC, DT>(p);
-    const size_t win = (size_t)waves * wb;
-    const size_t red = p.split > 1 ? (size_t)waves * NTX * FC * kLanes * sizeof(float2) : 0;
-    const size_t sh = win > red ? win : red;
-    const int64_t units = (int64_t)p.kp.n_tiles * (kWaves / p.n_wt) * nchunk;
-    auto launch = [&](const PlanDev& q, int64_t n) {
-        hipLaunchKernelGGL((das_kernel<FC, DT, NTX, kOne, kPlanar>), dim3((unsigned)n), dim3(waves * kLanes), sh, s, q, iq,
-                           reinterpret_cast<float2*>(out), __builtin_ctz(p.n_wt), __builtin_ctz(halves), __builtin_ctz(p.split), wb,
-                           p.n_vox * p.kp.F);
-    };
+// The plan's workgroups in launches of at most launch_units.
+template <typename Launch>
+static hipError_t launch_all(const PlanDev& p, int64_t units, Launch&& launch) {
     if (units <= p.launch_units) {
         launch(p, units);
     } else {
@@ -604,6 +685,31 @@ static hipError_t launch_k(const PlanDev& p, const void* iq, void* out, hipStrea
         }
     }
     return hipGetLastError();
+}
+
+template <int FC, int DT, int NTX>
+static hipError_t launch_gather(const PlanDev& p, const void* iq, void* out, hipStream_t s) {
+    const int halves = p.fc / FC, nchunk = (p.kp.F + p.fc - 1) / p.fc, waves = p.n_wt * halves * p.split;
+    const size_t sh = p.split > 1 ? (size_t)waves * NTX * FC * kLanes * sizeof(float2) : 0;
+    return launch_all(p, (int64_t)p.kp.n_tiles * (kWaves / p.n_wt) * nchunk, [&](const PlanDev& q, int64_t n) {
+        hipLaunchKernelGGL((das_gather_kernel<FC, DT, NTX>), dim3((unsigned)n), dim3(waves * kLanes), sh, s, q, iq,
+                           reinterpret_cast<float2*>(out), __builtin_ctz(p.n_wt), __builtin_ctz(halves), __builtin_ctz(p.split),
+                           p.n_vox * p.kp.F);
+    });
+}
+
+template <int FC, int DT, int NTX, bool kOne, bool kPlanar>
+static hipError_t launch_k(const PlanDev& p, const void* iq, void* out, hipStream_t s) {
+    const int halves = p.fc / FC, nchunk = (p.kp.F + p.fc - 1) / p.fc, waves = p.n_wt * halves * p.split;
+    const int wb = wave_bytes<FC, DT>(p);
+    const size_t win = (size_t)waves * wb;
+    const size_t red = p.split > 1 ? (size_t)waves * NTX * FC * kLanes * sizeof(float2) : 0;
+    const size_t sh = win > red ? win : red;
+    return launch_all(p, (int64_t)p.kp.n_tiles * (kWaves / p.n_wt) * nchunk, [&](const PlanDev& q, int64_t n) {
+        hipLaunchKernelGGL((das_kernel<FC, DT, NTX, kOne, kPlanar>), dim3((unsigned)n), dim3(waves * kLanes), sh, s, q, iq,
+                           reinterpret_cast<float2*>(out), __builtin_ctz(p.n_wt), __builtin_ctz(halves), __builtin_ctz(p.split), wb,
+                           p.n_vox * p.kp.F);
+    });
 }
 
 template <int FC, int DT, int NTX, bool kOne, bool kPlanar>
@@ -619,10 +725,26 @@ static hipError_t dispatch_ntx(const PlanDev& p, const void* iq, void* out, bool
     return prepare ? lds_limit<FC, DT, NTX, kOne, false>() : launch_k<FC, DT, NTX, kOne, false>(p, iq, out, s);
 }
 
+template <int FC, int DT, int NTX>
+static hipError_t dispatch_gather(const PlanDev& p, const void* iq, void* out, bool prepare, hipStream_t s) {
+    if (prepare)
+        return hipFuncSetAttribute((const void*)das_gather_kernel<FC, DT, NTX>, hipFuncAttributeMaxDynamicSharedMemorySize, kLdsBytes);
+    return launch_gather<FC, DT, NTX>(p, iq, out, s);
+}
+
 template <int FC, int DT>
 static hipError_t dispatch(const PlanDev& p, const void* iq, void* out, bool per_tx, bool prepare, hipStream_t s) {
+    if (p.cap_rows == kGather) {
+        if constexpr (FC <= kGatherFrames) {
+            if (p.per_tx && (prepare || per_tx)) {
+                const hipError_t e = dispatch_gather<FC, DT, kPerTx>(p, iq, out, prepare, s);
+                if (e != hipSuccess || per_tx) return e;
+            }
+        }
+        if constexpr (FC <= kGatherFrames) return dispatch_gather<FC, DT, 1>(p, iq, out, prepare, s);
+    }
     if constexpr (FC <= 2) {
-        if (prepare || per_tx) {
+        if (p.per_tx && (prepare || per_tx)) {
             const hipError_t e = dispatch_ntx<FC, DT, kPerTx, false>(p, iq, out, prepare, s);
             if (e != hipSuccess || per_tx) return e;
         }
@@ -674,7 +796,7 @@ hipError_t launch_das(const PlanDev& p, const void* iq, int dtype, void* out, hi
     return dispatch_dt(p, iq, dtype, out, false, false, s);
 }
 
-bool per_tx_supported(const PlanDev& p) { return p.fc <= 2 && p.kp.T <= kPerTx; }
+bool per_tx_supported(const PlanDev& p) { return p.per_tx; }
 
 hipError_t launch_das_per_tx(const PlanDev& p, const void* iq, int dtype, void* out, hipStream_t s) {
     if (p.kp.n_tiles == 0) return hipSuccess;
@@ -760,6 +882,23 @@ Variant choose_variant(int frames, int max_window, int64_t n_tiles, double items
     return best;
 }
 
+// Whether lanes gather their samples: where a wave's windows hold 100 rows and more on average, staging them costs more than
+// 64 lanes' own rows (scattered points, grids of steps of many samples).  F frames in chunks of FC, complex64, by mean rows:
+//   1 frame   91 rows  8.2 us staged, 9.1 gathered (128 x 128, 64 elements); 131 rows 63 and 46 (5000 points, 256 x 4 pairs);
+//             196 rows 13.1 and 5.2;
+//   8 frames  82 rows  287 and 305 (32 in all, 20,000 points); 116 rows 74 and 64; 173 rows 80 and 69.
+// 16 frames a wave stay staged (116 rows: 113 and 135 us; 173: 148 and 155).  Small launches cut their frames into small
+// chunks; gathering ones take more (the rows are read once instead of once a chunk, and groups make up for the workgroups):
+// 16 frames, 5000 points and 4 transmits 506 us in chunks of 1, 262 of 8; 8 frames, 8000 points 56 of 1, 39 of 2, 28 of 4,
+// but 1000 points 20, 22, 33.
+void choose_gather(PlanDev& p, double mean_rows) {
+    p.per_tx = p.fc <= 2 && p.kp.T <= kPerTx;
+    if (std::getenv("DAS_VARIANT") || p.fc >= 16 || mean_rows < 100.0) return;
+    p.cap_rows = kGather;
+    const int least = p.kp.F > 8 ? kGatherFrames : p.kp.F > 4 && p.kp.n_tiles >= 16 ? 4 : p.kp.F > 2 ? 2 : 1;
+    p.fc = std::max(p.fc, least);
+}
+
 // Workgroup shape and item length.
 //
 // Items: a window is cut only where its rows would take more than 10 KB of LDS (16 waves per CU), since every piece
@@ -771,17 +910,21 @@ Variant choose_variant(int frames, int max_window, int64_t n_tiles, double items
 // More groups pay where the launch stays short of 20000 waves and a group keeps 12 items (193 x 311, 3 transmits,
 // 7 frames: 46.5 -> 44.7 us; 16 groups from 32 items on: 63 x 32 x 32, 6 transmits, 1 frame 56.9 -> 50.7 us), or
 // where a group keeps 400 (96^3, 11 transmits: 3.27 -> 3.13 ms).  One group stays one where a wave tile has few items
-// (under 256): splitting gains nothing there (223 x 368 x 72 frames 171.5 / 171.7 us).
+// (under 256) and the launch holds many: splitting gains nothing there (223 x 368 x 72 frames 171.5 / 171.7 us).  Gathering
+// waves take no LDS but for their sums: 16 groups up to 8192 waves (3000 points, 1 frame 17.1 -> 11.7 us).
 void choose_split(PlanDev& p, int chunks, int max_wave_window, double items_per_tile) {
     const int fc = std::min(p.fc, 16), halves = p.fc / fc;  // frames per wave
     const int row = lds_row_bytes(fc);
     const int limit = p.pitch > 0 ? p.pitch - 1 : kMaxRows;
     int cap = std::max(1, std::min(max_wave_window, std::min(limit, kMaxRows)));
     cap = std::min(cap, 10 * 1024 / row - 1);
-    p.cap_rows = cap;
+    const bool gather = p.cap_rows == kGather;
+    if (!gather) p.cap_rows = cap;
     const int64_t units = (int64_t)p.kp.n_tiles * kWaves * chunks;
     int g = p.groups;
-    if (g > 1 || items_per_tile >= 256.0) {
+    if (gather) {
+        g = units * 16 <= 8192 ? 16 : units * 8 <= 20000 ? 8 : 4;
+    } else if (g > 1 || items_per_tile >= 256.0) {
         g = 4 / halves;
         if ((units * 8 <= 20000 && items_per_tile >= 8 * 12.0) || items_per_tile >= 8 * 400.0) g = 8;
         if (p.fc <= 4 && units * 16 <= 20000 && items_per_tile >= 16 * 32.0) g = 16;
@@ -792,8 +935,8 @@ void choose_split(PlanDev& p, int chunks, int max_wave_window, double items_per_
     const int rpi = fc <= 4 ? kLanes : kLanes / (fc / 4);
     auto waves = [&] { return (int64_t)p.n_wt * halves * p.split; };
     auto lds = [&] {
-        const int64_t ntx = fc <= 2 ? kPerTx : 1;
-        return std::max(waves() * (((cap + rpi) / rpi * rpi + 2) * row), waves() * ntx * fc * kLanes * 8);
+        const int64_t ntx = p.per_tx ? kPerTx : 1;
+        return std::max(gather ? 0 : waves() * (((cap + rpi) / rpi * rpi + 2) * row), waves() * ntx * fc * kLanes * 8);
     };
     // (wave tiles and groups stay powers of two)
     while (waves() * kLanes > kMaxThreads || lds() > kLdsBytes) (p.n_wt > 1 ? p.n_wt : p.split) /= 2;
