@@ -20,6 +20,10 @@
 
 #include "das_learn.h"
 
+// The loads straight to LDS are inline assembly that sets m0, the compiler's own register for that place; it warns of it in a
+// clobber list, which is where it has to stand so that no value is kept there across one.
+#pragma clang diagnostic ignored "-Winline-asm"
+
 namespace learn {
 
 typedef __attribute__((__vector_size__(8 * sizeof(short)))) short bf16x8;
@@ -354,12 +358,12 @@ __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __
     auto load = [&](const char* src, off_t off, uint32_t at, bool none) {
         if constexpr (k64) {
             const char* a = off < 0 || none ? reinterpret_cast<const char*>(kZeros) : src + off;
-            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(a) : "memory");
+            asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tglobal_load_lds_dwordx4 %1, off" ::"s"(at), "v"(a) : "memory", "m0");
         } else {
             const uint64_t a = reinterpret_cast<uint64_t>(src);
             const u32x4 rs = {(uint32_t)a, (uint32_t)(a >> 32) & 0xffffu, none ? 0u : 0x80000000u, 0x00020000u};
             asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(at), "v"(off), "s"(rs)
-                         : "memory");
+                         : "memory", "m0");
         }
     };
     const int64_t xslice = (kPerm ? sh.slice : (int64_t)vol.H * vol.W) * in_stride * 2,
@@ -539,7 +543,7 @@ __global__ __launch_bounds__(64 * WV, WV == 4 && kHold ? 3 : 4) void conv3d_bric
         const u32x4 rs = {(uint32_t)__builtin_amdgcn_readfirstlane((int)src),
                           (uint32_t)__builtin_amdgcn_readfirstlane((int)(src >> 32)) & 0xffffu, 0x80000000u, 0x00020000u};
         asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(to), "v"(off), "s"(rs)
-                     : "memory");
+                     : "memory", "m0");
     };
     // this lane's halo pieces: place in the halo (x, y, z; bit 31: outside the volume's rows or columns) and byte offset
     // from the halo's first voxel
