@@ -746,12 +746,45 @@ __global__ __launch_bounds__(64 * WV, WV == 4 && kHold ? 3 : 4) void conv3d_bric
     }
 }
 
+// What the weight gradient was formed from.
+struct WgradTensors {
+    const uint16_t* in;
+    const uint16_t* dy;
+    int in_stride, dy_stride;
+    Vol vol;
+    int Cin;
+};
+
+// A sum that is not finite, again from its terms in float64: with its zero pads the weight gradient kernel multiplies an
+// infinity or NaN of a block's side columns by a zero that is no term.  The terms are dy[v][n] * in[v + off(tap)][c], with
+// zeros outside the volume; tap < 0: dy[v][n].  One thread, 8 loads in flight, until the sum is a NaN.
+__device__ __forceinline__ float wgrad_terms(const WgradTensors& x, int n, int tap, int c) {
+    const int z = tap / 9 - 1, y = tap / 3 % 3 - 1, u = tap % 3 - 1;
+    const int64_t V = (int64_t)x.vol.D * x.vol.H * x.vol.W;
+    double s = 0.0;
+    for (int64_t v0 = 0; v0 < V && s == s; v0 += 8) {
+        float g[8], q[8];
+#pragma unroll
+        for (int k = 0; k < 8; ++k) {
+            const int64_t v = v0 + k < V ? v0 + k : V - 1;
+            const int w = (int)(v % x.vol.W) + u, h = (int)(v / x.vol.W % x.vol.H) + y, d = (int)(v / ((int64_t)x.vol.W * x.vol.H)) + z;
+            const bool inside = (unsigned)w < (unsigned)x.vol.W && (unsigned)h < (unsigned)x.vol.H && (unsigned)d < (unsigned)x.vol.D;
+            g[k] = bf2f(x.dy[v * x.dy_stride + n]);
+            q[k] = tap < 0 ? 1.0f : inside ? bf2f(x.in[(((int64_t)d * x.vol.H + h) * x.vol.W + w) * x.in_stride + c]) : 0.0f;
+        }
+#pragma unroll
+        for (int k = 0; k < 8; ++k)
+            if (v0 + k < V) s += (double)g[k] * q[k];
+    }
+    return (float)s;
+}
+
 // dw[i] = sum_b part[b][i], i over Cout * K, and the same for db (the blocks past the first nwb): 32 outputs per
 // workgroup, the parts split over 8 thread rows (row r sums parts r, r + 8, ... in order), the 8 row sums added in row
 // order: deterministic.
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restrict__ part, const float* __restrict__ part_db,
                                                            int nparts, int64_t nw, int nwb, int nb,
-                                                           float* __restrict__ dw, float* __restrict__ db) {
+                                                           float* __restrict__ dw, float* __restrict__ db, WgradTensors x) {
     __shared__ float red[8][32];
     const int col = threadIdx.x & 31, row = threadIdx.x >> 5;
     const bool is_db = (int)blockIdx.x >= nwb;
@@ -778,6 +811,10 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
         float t = red[0][col];
 #pragma unroll
         for (int r = 1; r < 8; ++r) t += red[r][col];
+        if (!(fabsf(t) < __builtin_inff())) {
+            const int k = (int)(i % (27 * x.Cin));
+            t = is_db ? wgrad_terms(x, (int)i, -1, 0) : wgrad_terms(x, (int)(i / (27 * x.Cin)), k / x.Cin, k % x.Cin);
+        }
         (is_db ? db : dw)[i] = t;
     }
 }
@@ -1511,8 +1548,10 @@ int das_conv3d_wgrad(const void* in, int in_stride, int in_coff, const void* dy,
     const int parts = launch_wgrad(nparts, s, reinterpret_cast<const uint16_t*>(in), in_stride, in_coff,
                                    reinterpret_cast<const uint16_t*>(dy), dy_stride, dy_coff, part, part_db,
                                    learn::Vol{D, H, W}, cin, cout);
+    const learn::WgradTensors tensors{reinterpret_cast<const uint16_t*>(in) + in_coff, reinterpret_cast<const uint16_t*>(dy) + dy_coff,
+                                      in_stride, dy_stride, learn::Vol{D, H, W}, cin};
     hipLaunchKernelGGL(learn::reduce_parts_kernel, dim3(blocks_for(nw, 32) + blocks_for(cout, 32)), dim3(256), 0, s, part,
-                       part_db, parts, nw, (int)blocks_for(nw, 32), cout, dw, db);
+                       part_db, parts, nw, (int)blocks_for(nw, 32), cout, dw, db, tensors);
     return launch_status("wgrad launch failed");
 }
 
