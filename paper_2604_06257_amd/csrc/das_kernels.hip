@@ -882,20 +882,23 @@ Variant choose_variant(int frames, int max_window, int64_t n_tiles, double items
     return best;
 }
 
-// Whether lanes gather their samples: where a wave's windows hold 100 rows and more on average, staging them costs more than
-// 64 lanes' own rows (scattered points, grids of steps of many samples).  F frames in chunks of FC, complex64, by mean rows:
-//   1 frame   91 rows  8.2 us staged, 9.1 gathered (128 x 128, 64 elements); 131 rows 63 and 46 (5000 points, 256 x 4 pairs);
-//             196 rows 13.1 and 5.2;
-//   8 frames  82 rows  287 and 305 (32 in all, 20,000 points); 116 rows 74 and 64; 173 rows 80 and 69.
-// 16 frames a wave stay staged (116 rows: 113 and 135 us; 173: 148 and 155).  Small launches cut their frames into small
-// chunks; gathering ones take more (the rows are read once instead of once a chunk, and groups make up for the workgroups):
-// 16 frames, 5000 points and 4 transmits 506 us in chunks of 1, 262 of 8; 8 frames, 8000 points 56 of 1, 39 of 2, 28 of 4,
-// but 1000 points 20, 22, 33.
+// Whether lanes gather their samples: where a wave's windows hold many rows on average (scattered points, grids of steps of
+// many samples), staging them costs more than 64 lanes' own rows.  Staged and gathered, complex64, us by mean rows:
+//   1 frame a chunk    58 rows 7.2, 8.9 (128 x 128, 64 elements); 68 rows 8.1, 5.2; 82 rows 25.8, 18.1 (20,000 points, 256
+//                      elements); 131 rows 63, 46 (5000 points, 256 x 4 pairs); 196 rows 13.1, 5.2;
+//   2                  68 rows 13.9, 14.9; 82 rows 239, 207; 131 rows 1538, 751;
+//   4                  82 rows 471, 548; 113 rows 175, 157; 135 rows 36.9, 32.7;
+//   8                  82 rows 287, 305; 116 rows 74, 64; 173 rows 80, 69;
+//   16                 116 rows 113, 135; 173 rows 148, 155: always staged.
+// Small launches cut their frames into small chunks; gathering ones of some tiles take more frames (the rows are read once
+// instead of once a chunk, and groups make up for the workgroups): 16 frames, 5000 points (20 tiles) and 4 transmits 506 us in
+// chunks of 1, 262 of 8; 8 frames, 8000 points (32 tiles) 56 of 1, 39 of 2, 28 of 4; but 1000 points (4 tiles) 20, 22, 33.
 void choose_gather(PlanDev& p, double mean_rows) {
     p.per_tx = p.fc <= 2 && p.kp.T <= kPerTx;
-    if (std::getenv("DAS_VARIANT") || p.fc >= 16 || mean_rows < 100.0) return;
+    if (std::getenv("DAS_VARIANT") || p.fc >= 16 || mean_rows < (p.fc == 1 ? 64.0 : p.fc == 2 ? 80.0 : 100.0)) return;
     p.cap_rows = kGather;
-    const int least = p.kp.F > 8 ? kGatherFrames : p.kp.F > 4 && p.kp.n_tiles >= 16 ? 4 : p.kp.F > 2 ? 2 : 1;
+    const int frames = p.kp.F, tiles = p.kp.n_tiles;
+    const int least = tiles < 12 ? 1 : frames > 8 ? kGatherFrames : frames > 4 && tiles >= 16 ? 4 : frames > 2 ? 2 : 1;
     p.fc = std::max(p.fc, least);
 }
 
