@@ -98,7 +98,10 @@ typedef struct das_plan das_plan;
  *   stream      hipStream_t used for the uploads and set-up kernels; the call
  *               synchronises it before returning.
  * The plan copies what it needs: the caller may free all inputs afterwards.
- * Allocates device memory proportional to V * (T + 4) + E plus the tiling. */
+ * Allocates device memory proportional to V * (T + 4) + E plus the tiling, and 16
+ * bytes of work list per transmit and element that a wave of 64 voxels sees
+ * (96^3 voxels, 1024 elements, 5 transmits at f-number 1: 390 MB; 11 transmits
+ * 870 MB); up to 4 GiB more until it returns. */
 int das_plan_create(das_plan **out, const das_params *p, const float *elem_xyz,
                     const float *vox_xyz, const float *tx_arrival, void *stream);
 
@@ -151,9 +154,10 @@ typedef struct das_plan_info {
     int64_t total_triples;     /* V * E * T (Eq. 1 points per frame)           */
     int64_t active_triples;    /* (voxel, element, transmit) with w > 0 and the
                                   delayed sample inside the record             */
-    int64_t processed_triples; /* (slot, element, transmit) the kernel visits:
-                                  valid slots of tiles whose window for (t, e)
-                                  is not empty (tile-granular aperture)        */
+    int64_t processed_triples; /* valid (slot, element, transmit) of tiles whose
+                                  window for (t, e) is not empty (tile-granular
+                                  aperture; the kernels skip those that none of
+                                  a wave's 64 slots contributes to)            */
     int32_t tile_dims[3];      /* lattice points per tile along x, y, z (0 when
                                   the points are not a lattice)                */
     int32_t max_window;        /* largest per-tile sample window (rows)        */
@@ -162,8 +166,9 @@ typedef struct das_plan_info {
     int32_t kernel_pitch;      /*   most window rows per work item + 1 (0: only
                                       the LDS bounds them; -1: windows of many
                                       rows, lanes gather their samples),       */
-    int32_t kernel_groups;     /*   element groups per tile, at least (a plan
-                                      may split its waves' items further)      */
+    int32_t kernel_groups;     /*   element groups: 1 may leave a wave's items
+                                      whole, more split them (how far, up to 16,
+                                      follows from the launch's size)          */
 } das_plan_info;
 
 /* Fill `info` (host) for `plan`.  Host-only, synchronous. */
@@ -197,7 +202,8 @@ int das_version(void);
 
 /* The beamforming kernel variants, as (frames per workgroup, most window rows
  * per work item + 1, element groups) triples, 0 rows leaving the item length
- * to the LDS; das_plan_info reports which one a plan uses.
+ * to the LDS; das_plan_info reports which one a plan uses (plans whose lanes
+ * gather their samples may take more frames per workgroup).
  *   fc_pitch_groups  host int32 [3 * capacity] or NULL: receives the first
  *                    min(count, capacity) triples.
  *   capacity         >= 0 (0 with NULL asks for the count only).
@@ -208,7 +214,8 @@ int das_version(void);
  * window and the tile count.  For tuning and tests, the environment variable
  * DAS_VARIANT="fc,pitch,groups", read at plan creation, forces a listed
  * variant when fc is at most twice the frames per workgroup the plan would
- * choose (any fc up to 32 when F >= 32); otherwise it is ignored.  Every
+ * choose (any fc up to 32 when F >= 32); otherwise it is ignored.  A plan made
+ * under it stages its windows however long they are.  Every
  * variant computes the same sums (element groups fold their partial sums in
  * a different order, so results may differ in the last bits). */
 int das_kernel_variants(int32_t *fc_pitch_groups, int32_t capacity);

@@ -805,8 +805,8 @@ hipError_t launch_das_per_tx(const PlanDev& p, const void* iq, int dtype, void* 
 
 // ------------------------------------------------------------ variant rule
 // A variant says how a plan cuts its work: FC frames per workgroup (waves of up to 16 frames; 32 in two halves), items
-// of at most P - 1 window rows (P = 0: only the LDS bounds them), G element groups per tile of 4 waves at least
-// (choose_split adds groups).
+// of at most P - 1 window rows (P = 0: only the LDS bounds them), and whether (G > 1) element groups share a wave tile's
+// items; it is kernel code for FC only.
 #define DAS_VARIANTS(X)                                                                              \
     X(32, 41, 3) X(32, 49, 3) X(32, 33, 2) X(32, 65, 2) X(16, 33, 2) X(16, 65, 2) X(16, 129, 2) X(8, 33, 1) X(8, 65, 1)       \
     X(8, 129, 1) X(8, 257, 1) X(4, 33, 1) X(4, 65, 1) X(4, 129, 1) X(4, 257, 1) X(4, 513, 1) X(2, 129, 1)      \
@@ -826,7 +826,8 @@ hipError_t launch_das_per_tx(const PlanDev& p, const void* iq, int dtype, void* 
 //  - the pitch is the smallest that holds the longest tile window in one piece; one or two frames per workgroup on
 //    tiles of fewer than 1200 items leave it open (P = 0);
 //  - a launch should hold about 6144 waves (FC <= 4) or 2560 waves (FC >= 8), or 8192 when tiles carry 1024 or more
-//    items on average: element groups are added until it does, up to 4.
+//    items on average: element groups are added until it does, up to 4.  For the launch they say whether a wave tile's items
+//    are split at all (more than 1); how far, choose_split sets.
 static bool variant_exists(int fc, int pitch, int g) {
 #define DAS_HAS(FC_, P_, G_) \
     if (FC_ == fc && P_ == pitch && G_ == g) return true;
@@ -934,6 +935,13 @@ void choose_split(PlanDev& p, int chunks, int max_wave_window, double items_per_
     }
     p.split = g;
     p.n_wt = std::max(1, kWaves / (g * halves));
+    int want[2] = {0, 0};
+    if (const char* env = std::getenv("DAS_SPLIT"))  // tuning override: "groups,wave tiles", powers of two
+        if (std::sscanf(env, "%d,%d", &want[0], &want[1]) == 2 && want[0] >= 1 && want[0] <= 16 && !(want[0] & (want[0] - 1)) &&
+            (want[1] == 1 || want[1] == 2 || want[1] == 4)) {
+            p.split = want[0];
+            p.n_wt = want[1];
+        }
     // the most that any IQ type's launch asks for
     const int rpi = fc <= 4 ? kLanes : kLanes / (fc / 4);
     auto waves = [&] { return (int64_t)p.n_wt * halves * p.split; };
