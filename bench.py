@@ -291,8 +291,8 @@ def c3_report(steps, warmup, torch, das, oracle):
 def hbm_report(T, E, S, F, V, info, ms, traffic):
     """The HBM side of the roofline for one launch: compulsory bytes (IQ read once, output written once, the
     transmit table and the voxel and element coordinates), their rate against the 8 TB/s peak, the measured HBM
-    bytes (PMC record) as a rate, and the kernel's on-chip gather rate (16 B of LDS operands per processed point
-    and frame)."""
+    bytes (PMC record) as a rate, and an upper bound of the kernel's on-chip gather rate (16 B of LDS operands per
+    point and frame of the processed triples, which are counted by whole tiles: a wave skips more)."""
     compulsory = T * E * S * F * 8 + V * F * 8 + T * V * 4 + V * 12 + E * 12
     sec = ms * 1e-3
     rep = {"compulsory_bytes": compulsory, "compulsory_GBps": compulsory / sec / 1e9,

@@ -7,7 +7,9 @@
 // numbers with 32 fraction bits, because an FP32 phase loses ~1e-5 cycles and
 // caps the error near -85 dB.  The fractional phase, the interpolation weight
 // and the apodization weight are then taken to FP32 for the multiply-accumulate
-// (a rounding of up to 3e-8, against 2^-33 = 1.2e-10 of the fixed point).
+// (a rounding of up to 3e-8, against 2^-33 = 1.2e-10 of the fixed point): over
+// 32 calls the errors against 64 bits of this form and of one that keeps FP64 up
+// to the fraction are 0.9987-1.0015 of each other, 0.99998 in the mean.
 //
 // Fixed point without conversions: adding 1.5 * 2^20 to a double within +-2^19
 // leaves 32 fraction bits, so the FMA that forms the sum also rounds it there;

@@ -625,7 +625,8 @@ void das_gather_kernel(PlanDev p, const void* __restrict__ iq, float2* __restric
 }
 
 // Any finite geometry: FP64 delays and phases, samples gathered from the record, every (element, transmit) visited.
-// Serves only plans whose delays or phases leave the fixed point's range or whose sizes do not fit an item.
+// Serves only plans whose own rows span 2^19 and more, whose phases over the record do not fit 2^19 cycles, or whose sizes
+// do not fit an item (more than 16384 transmits or 262144 elements, records of more than 2^45 samples).
 template <int DT>
 __global__ __launch_bounds__(kSlots) void das_wide_kernel(PlanDev p, const void* __restrict__ iq,
                                                           float2* __restrict__ out, int per_tx, int64_t tx_stride) {

@@ -4,12 +4,13 @@
 // a wider buffer (row stride `*_stride` channels, first channel `*_coff`).
 //
 // Convolution (3 x 3 x 3, zero padding, stride 1) as an implicit GEMM on
-// v_mfma_f32_16x16x32_bf16: M = voxels, N = output channels, K = 27 * Cin with
-// k = tap * Cin + c.  One wave owns 16 voxels and all output channels; per K
-// step of 32 each lane loads 8 consecutive input channels of one tap (16 B)
-// for its voxel (operand A) and 8 consecutive weights of one output channel
-// (operand B).  With `flip`, the taps are mirrored: this is the input gradient
-// of a convolution when the weights are passed transposed ([Cin][27][Cout]).
+// v_mfma_f32_16x16x32_bf16: voxels and output channels are the tile's two sides,
+// K = 27 * Cin in steps of 32, ordered by channel chunk, in-plane tap and depth
+// tap.  A workgroup stages a brick of the input with its one-voxel halo in LDS,
+// one channel chunk at a time (conv3d_brick_kernel for aligned tensors,
+// conv3d_kernel for the others; the same bits).  With `flip`, the taps are
+// mirrored: this is the input gradient of a convolution when the weights are
+// passed transposed ([Cin][27][Cout]).
 #include <hip/hip_bf16.h>
 #include <hip/hip_runtime.h>
 
@@ -267,7 +268,8 @@ __global__ __launch_bounds__(256) void conv3d_kernel(const uint16_t* __restrict_
 // column offset dy's (by the opposite amount): 9 input and 3 dy fragments per step for 27 MFMAs, where one shifted input
 // per tap would be 28.  The input's pad columns are zeros, and so are dy's at the volume's sides.  Waves w and w + 4 (one
 // SIMD) take every fourth step of 32 voxels, w for 15 of the taps, w + 4 for the other 12 and the bias gradient (dy
-// times a fragment of ones), so that a wave stays within 128 registers.
+// times a fragment of ones), so that a wave needs little more than the 128 registers that let two workgroups share a CU: 5
+// are spilled (29 in the 64-bit form, 15 and 27 with permuted axes), read back where slices are asked for, not between MFMAs.
 //
 // MFMA-bound in the steps (27 x 16 cycles per 32 voxels and SIMD), with staging and the final sums on top.  A wave per
 // (chunk, tap) staging transposed copies of its own had re-read both tensors 27 times:
