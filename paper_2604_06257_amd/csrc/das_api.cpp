@@ -497,7 +497,7 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
     for (int64_t k = 0; k < E; ++k)
         for (int a = 0; a < 3; ++a) elemd[4 * k + a] = (double)elem[3 * k + a];
     unsigned long long* counts = nullptr;
-    unsigned long long hc[7] = {0, 0, 0, 0, 0, 0, 0};
+    unsigned long long hc[6] = {0, 0, 0, 0, 0, 0};
     int2* win = nullptr;
     int32_t* n_items = nullptr;
     const int64_t n_wt = tl.n_tiles * das::kWaves;
@@ -536,13 +536,9 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
         d.fc = var.fc;
         d.pitch = var.pitch;
         d.groups = var.groups;
-        das::choose_gather(d, hc[6] > 0 ? (double)hc[5] / (double)hc[6] : 0.0);
+        das::choose_gather(d, hc[5] > 0 ? (double)hc[4] / (double)hc[5] : 0.0);
         const int chunks = (p->n_frames + d.fc - 1) / d.fc;
         das::choose_split(d, chunks, (int)std::min<unsigned long long>(hc[3], INT32_MAX), items_per_tile);
-        if (hc[4] > (unsigned long long)INT32_MAX) {  // the most (tile, element, transmit) windows that a plan holds
-            e = hipErrorInvalidValue;
-            goto hip_fail;
-        }
         std::vector<uint32_t> off((size_t)n_wt + 1, 0);
         if (n_wt > 0 && !kp.wide) {
             std::vector<int32_t> n((size_t)n_wt);
@@ -552,24 +548,32 @@ int das_plan_create(das_plan** out, const das_params* p, const float* elem_xyz, 
                 (e = hipMemcpyAsync(n.data(), n_items, n_wt * sizeof(int32_t), hipMemcpyDeviceToHost, s)) != hipSuccess ||
                 (e = hipStreamSynchronize(s)) != hipSuccess)
                 goto hip_fail;
-            uint64_t sum = 0;
+            // A list longer than its offsets can count, or of more than 2^31 items that do not fit the memory: the general
+            // kernel needs none.
+            uint64_t sum = 0, most = UINT32_MAX;
+            if (const char* env = std::getenv("DAS_ITEMS"))  // tuning override: most pairs of items
+                most = std::min<uint64_t>(most, std::strtoull(env, nullptr, 10));
             for (int64_t k = 0; k < n_wt; ++k) {
                 sum += (uint64_t)n[(size_t)k] / 2;
-                if (n[(size_t)k] >= INT32_MAX - 1 || sum > UINT32_MAX) {
-                    e = hipErrorInvalidValue;
-                    goto hip_fail;
-                }
+                if (n[(size_t)k] >= INT32_MAX - 1) sum = most + 1;
+                if (sum > most) break;
                 off[(size_t)k + 1] = (uint32_t)sum;
             }
+            if (sum <= most) e = hipMalloc((void**)&d.items, (2 * (size_t)sum + das::kItemPad) * sizeof(int4));
+            if (sum > most || (e == hipErrorOutOfMemory && 2 * sum > (uint64_t)INT32_MAX)) {
+                (void)hipGetLastError();
+                e = hipSuccess;
+                kp.wide = 1;
+                std::fill(off.begin(), off.end(), 0u);
+            }
+            if (e != hipSuccess) goto hip_fail;
         }
         std::vector<int4> order;
         for (const int32_t u : das::order_units(tl, off, d.n_wt, chunks)) {
             const int32_t wt = u / chunks * d.n_wt;
             order.push_back(make_int4(wt, u % chunks, (int)off[(size_t)wt], (int)(off[(size_t)wt + 1] - off[(size_t)wt])));
         }
-        if ((e = hipMalloc((void**)&d.items, (2 * (size_t)off.back() + das::kItemPad) * sizeof(int4))) != hipSuccess ||
-            (e = upload(&d.item_off, off, s)) != hipSuccess || (e = upload(&d.wg_unit, order, s)) != hipSuccess)
-            goto hip_fail;
+        if ((e = upload(&d.item_off, off, s)) != hipSuccess || (e = upload(&d.wg_unit, order, s)) != hipSuccess) goto hip_fail;
         if (!kp.wide && (e = for_slabs([&](int t, int n) {
                              return das::launch_items(d, t, n, win, d.item_off, d.items, nullptr, s);
                          })) != hipSuccess)

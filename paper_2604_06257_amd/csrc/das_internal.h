@@ -103,8 +103,7 @@ int list_variants(int32_t* out, int capacity);
 // counts[0] = active (slot, e, t) triples (w > 0, inside the record);
 // counts[1] = processed triples (valid slots of tiles whose window is not
 // empty); counts[2] = longest tile window; counts[3] = longest wave window;
-// counts[4] = tile windows that are not empty; counts[5], counts[6] = rows and
-// number of the wave windows that are not empty.
+// counts[4], counts[5] = rows and number of the wave windows that are not empty.
 hipError_t launch_windows(const PlanDev& p, int tile0, int n, int2* win, unsigned long long* counts, hipStream_t s);
 
 // Items of those tiles' wave tiles (pieces of at most cap_rows rows): their numbers, even and at most INT32_MAX - 1 (items =

@@ -127,8 +127,8 @@ __global__ __launch_bounds__(kSlots) void window_kernel(PlanDev p, int tile0, in
     if (lane == 0) {
         atomicAdd(&counts[0], active);
         atomicMax(&counts[3], (unsigned long long)longest);
-        atomicAdd(&counts[5], rows);
-        atomicAdd(&counts[6], (unsigned long long)used);
+        atomicAdd(&counts[4], rows);
+        atomicAdd(&counts[5], (unsigned long long)used);
     }
 }
 
@@ -166,7 +166,6 @@ __global__ __launch_bounds__(kSlots) void window_stats_kernel(PlanDev p, int til
     __syncthreads();
     if (threadIdx.x == 0) {
         atomicAdd(&counts[1], s_n * (unsigned long long)s_valid);
-        atomicAdd(&counts[4], s_n);
         atomicMax(&counts[2], (unsigned long long)s_max);
     }
 }
@@ -625,8 +624,9 @@ void das_gather_kernel(PlanDev p, const void* __restrict__ iq, float2* __restric
 }
 
 // Any finite geometry: FP64 delays and phases, samples gathered from the record, every (element, transmit) visited.
-// Serves only plans whose own rows span 2^19 and more, whose phases over the record do not fit 2^19 cycles, or whose sizes
-// do not fit an item (more than 16384 transmits or 262144 elements, records of more than 2^45 samples).
+// Serves only plans whose own rows span 2^19 and more, whose phases over the record do not fit 2^19 cycles, whose sizes do
+// not fit an item (more than 16384 transmits or 262144 elements, records of more than 2^45 samples), or whose items fit neither
+// 2^32 pairs nor the memory.
 template <int DT>
 __global__ __launch_bounds__(kSlots) void das_wide_kernel(PlanDev p, const void* __restrict__ iq,
                                                           float2* __restrict__ out, int per_tx, int64_t tx_stride) {

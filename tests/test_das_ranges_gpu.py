@@ -108,6 +108,19 @@ def test_high_carrier_in_a_slowly_sampled_record():
         assert (kernel == GENERAL) == general and db <= -100.0
 
 
+@pytest.mark.parametrize("T,F,per_tx", [(1, 1, False), (3, 2, True), (2, 9, False)])
+def test_lists_of_too_many_items_take_the_general_kernel(T, F, per_tx, monkeypatch):
+    """Three wave tiles of 33 elements and up to 3 transmits: at least 49 pairs of items, at most a few hundred."""
+    elem = linear_array(33, 0.3e-3)
+    vox = column(n=192, z0=9e-3, step=1e-5)
+    tx = np.stack([(vox[:, 2] / C + 1e-7 * t).astype(np.float32) for t in range(T)])
+    iq = random_iq((T, 33, 700, F), seed=12)
+    for pairs, general in ((20, True), (10_000, False)):
+        monkeypatch.setenv("DAS_ITEMS", str(pairs))
+        kernel, db = run(iq, elem, vox, tx, per_tx=per_tx)
+        assert (kernel == GENERAL) == general and db <= -100.0
+
+
 def test_item_lists_beyond_32_bits_keep_the_staged_kernel():
     """2.4e9 work items (39 GB): 2,344 wave tiles that see every one of 16,384 x 64 (element, transmit) pairs."""
     T, E, S, V = 64, 16_384, 64, 150_000
