@@ -280,7 +280,7 @@ constexpr int kWgThreads = 512, kWgWaves = 8, kWgSplit = 4;  // kWgSplit: waves 
 constexpr int kWgX = 6, kWgY = 5;               // KiB of an input and of a dy slice that a wave loads, at most
 constexpr int kWgTiles = 15;                    // accumulator tiles of a wave: 5 (depth, row) offsets x 3, or 4 x 3
                                                 // and the bias gradient
-constexpr int kWgPhase = 8;                     // tiles of a wave summed at a time
+constexpr int kWgPhase = 8;                     // tiles of a wave summed at a time (3 i and 3 i + 1 together)
 typedef uint32_t u32x4 __attribute__((ext_vector_type(4)));
 typedef short v4s __attribute__((ext_vector_type(4)));
 typedef __bf16 bf16v4 __attribute__((ext_vector_type(4)));
@@ -453,6 +453,9 @@ __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __
     }
     // The four waves of a tap half: all tiles through LDS, kWgPhase at a time, each wave sums every fourth tile in the
     // waves' order and stores it.
+    //
+    // In a block's first row nothing pairs dy's first column with the input's pad before it.  The first wave's sum of the tap
+    // beside (the same gradient times the first column) is added times zero instead, so that an infinity or NaN shows.
     float* const red = reinterpret_cast<float*>(lds);  // [upper][tile][share][64 lanes] x 4
     const int c = c0 + (lane & 15), ntiles = upper ? (c0 == 0 ? 14 : 12) : 15;
     float* const pb = part + ((int64_t)my_part * Cout + n0 + 4 * (lane >> 4)) * 27 * Cin + c;
@@ -468,7 +471,11 @@ __global__ __launch_bounds__(kWgThreads, 4) void wgrad_kernel(const uint16_t* __
 #pragma unroll
             for (int w = 0; w < kWgSplit; ++w)
                 v[w] = *reinterpret_cast<const f32x4*>(&red[(((upper * kWgPhase + t - p0) * kWgSplit + w) * 64 + lane) * 4]);
-            const f32x4 y = ((v[0] + v[1]) + v[2]) + v[3];
+            const f32x4 b = *reinterpret_cast<const f32x4*>(
+                &red[((upper * kWgPhase + t + (t % 3 == 0 ? 1 : 0) - p0) * kWgSplit * 64 + lane) * 4]);
+            f32x4 y = ((v[0] + v[1]) + v[2]) + v[3];
+#pragma unroll
+            for (int r = 0; r < 4; ++r) y[r] = fmaf(0.0f, b[r], y[r]);
             if (upper && t >= 12) {  // dy (unshifted: tile 13) times ones: every column holds the bias gradient's rows
                 if (t == 13 && (lane & 15) == 0)
 #pragma unroll
@@ -748,42 +755,58 @@ __global__ __launch_bounds__(64 * WV, WV == 4 && kHold ? 3 : 4) void conv3d_bric
     }
 }
 
-// What the weight gradient was formed from.
+// What the weight gradient was formed from, as it was walked (tap_* and the strides of `sh` set in either order of axes).
 struct WgradTensors {
     const uint16_t* in;
     const uint16_t* dy;
-    int in_stride, dy_stride;
+    int in_stride, dy_stride, Cin;
     Vol vol;
-    int Cin;
+    WgradShape sh;
 };
 
-// A sum that is not finite, again from its terms in float64: with its zero pads the weight gradient kernel multiplies an
-// infinity or NaN of a block's side columns by a zero that is no term.  The terms are dy[v][n] * in[v + off(tap)][c], with
-// zeros outside the volume; tap < 0: dy[v][n].  One thread, 8 loads in flight, until the sum is a NaN.
-__device__ __forceinline__ float wgrad_terms(const WgradTensors& x, int n, int tap, int c) {
-    const int z = tap / 9 - 1, y = tap / 3 % 3 - 1, u = tap % 3 - 1;
-    const int64_t V = (int64_t)x.vol.D * x.vol.H * x.vol.W;
-    double s = 0.0;
-    for (int64_t v0 = 0; v0 < V && s == s; v0 += 8) {
-        float g[8], q[8];
+// A part's sum that is not finite, again from its terms in float64: with its zero pads wgrad_kernel multiplies an infinity or
+// NaN of a block's side columns by a zero that is no term.  The terms are dy[v][n] * in[v + off(tap)][c], with zeros outside
+// the volume; tap < 0: dy[v][n].  Every second row, from `row` on, until the sum is a NaN.
+//
+// A block's terms are those whose input column it holds; the one past the volume's side goes with the side's own.
+__device__ __forceinline__ double wgrad_terms(const WgradTensors& x, int part, int n, int tap, int c, int row) {
+    const WgradShape& sh = x.sh;
+    const Vol& vol = x.vol;
+    const int oz = tap < 0 ? 0 : tap / sh.tap_slice % 3 - 1, oy = tap < 0 ? 0 : tap / sh.tap_row % 3 - 1,
+              u = tap < 0 ? 0 : tap / sh.tap_col % 3 - 1;
+    const int64_t total = (int64_t)sh.nyb * sh.nwb * vol.D;
+    const int64_t s0 = total * part / sh.parts, s1 = total * (part + 1) / sh.parts;
+    double sum = 0.0;
+    for (int64_t s = s0; s < s1; ++s) {
+        const int z = (int)(s % vol.D), blk = (int)(s / vol.D);
+        const int h0 = blk % sh.nyb * sh.bh, h1 = min(h0 + sh.bh, vol.H), w0 = blk / sh.nyb * sh.wb, w1 = min(w0 + sh.wb, vol.W);
+        const int from = w0 == 0 ? 0 : w0 - u, to = w1 == vol.W ? vol.W : w1 - u;
+        for (int h = h0 + ((row ^ (int)s) & 1); h < h1; h += 2) {
+            const bool inside = (unsigned)(z + oz) < (unsigned)vol.D && (unsigned)(h + oy) < (unsigned)vol.H;
+            const int64_t at = z * sh.slice + h * sh.row;
+            const uint16_t* const yp = x.dy + at * x.dy_stride + n;
+            const uint16_t* const xp = x.in + (at + oz * sh.slice + oy * sh.row + u * sh.col) * x.in_stride + c;
+            for (int w = from; w < to && sum == sum; w += 4) {
+                float g[4], q[4];
 #pragma unroll
-        for (int k = 0; k < 8; ++k) {
-            const int64_t v = v0 + k < V ? v0 + k : V - 1;
-            const int w = (int)(v % x.vol.W) + u, h = (int)(v / x.vol.W % x.vol.H) + y, d = (int)(v / ((int64_t)x.vol.W * x.vol.H)) + z;
-            const bool inside = (unsigned)w < (unsigned)x.vol.W && (unsigned)h < (unsigned)x.vol.H && (unsigned)d < (unsigned)x.vol.D;
-            g[k] = bf2f(x.dy[v * x.dy_stride + n]);
-            q[k] = tap < 0 ? 1.0f : inside ? bf2f(x.in[(((int64_t)d * x.vol.H + h) * x.vol.W + w) * x.in_stride + c]) : 0.0f;
+                for (int k = 0; k < 4; ++k) {
+                    const int64_t wk = min(w + k, to - 1);
+                    g[k] = bf2f(yp[wk * sh.col * x.dy_stride]);
+                    q[k] = tap < 0 ? 1.0f : inside && (unsigned)((int)wk + u) < (unsigned)vol.W ? bf2f(xp[wk * sh.col * x.in_stride]) : 0.0f;
+                }
+#pragma unroll
+                for (int k = 0; k < 4; ++k)
+                    if (w + k < to) sum += (double)g[k] * q[k];
+            }
         }
-#pragma unroll
-        for (int k = 0; k < 8; ++k)
-            if (v0 + k < V) s += (double)g[k] * q[k];
     }
-    return (float)s;
+    return sum;
 }
 
 // dw[i] = sum_b part[b][i], i over Cout * K, and the same for db (the blocks past the first nwb): 32 outputs per
 // workgroup, the parts split over 8 thread rows (row r sums parts r, r + 8, ... in order), the 8 row sums added in row
-// order: deterministic.
+// order: deterministic.  Sums that are not finite: the parts that are not, again from their terms (16 -> 16 channels at 96^3
+// with one infinity: 0.3 to 0.7 ms; 376 when one thread formed a whole sum, 0.035 without the infinity).
 __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restrict__ part, const float* __restrict__ part_db,
                                                            int nparts, int64_t nw, int nwb, int nb,
                                                            float* __restrict__ dw, float* __restrict__ db, WgradTensors x) {
@@ -809,16 +832,27 @@ __global__ __launch_bounds__(256) void reduce_parts_kernel(const float* __restri
     }
     red[row][col] = s;
     __syncthreads();
-    if (row == 0 && i < n) {
-        float t = red[0][col];
+    if (row > 1) return;
+    float t = red[0][col];
 #pragma unroll
-        for (int r = 1; r < 8; ++r) t += red[r][col];
-        if (!(fabsf(t) < __builtin_inff())) {
-            const int k = (int)(i % (27 * x.Cin));
-            t = is_db ? wgrad_terms(x, (int)i, -1, 0) : wgrad_terms(x, (int)(i / (27 * x.Cin)), k / x.Cin, k % x.Cin);
+    for (int r = 1; r < 8; ++r) t += red[r][col];
+    if (i < n && !(fabsf(t) < __builtin_inff())) {
+        double sum = 0.0;
+        const int k = (int)(i % (27 * x.Cin));
+        const int ch = is_db ? (int)i : (int)(i / (27 * x.Cin)), tap = is_db ? -1 : k / x.Cin, c = is_db ? 0 : k % x.Cin;
+        for (int b0 = 0; b0 < nparts && sum == sum; b0 += 8) {
+            unsigned bad = 0;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                const float v = src[(int64_t)min(b0 + j, nparts - 1) * n + i];
+                const bool finite = fabsf(v) < __builtin_inff();
+                if (b0 + j < nparts) sum += finite && row == 0 ? v : 0.0f, bad |= finite ? 0u : 1u << j;
+            }
+            for (; bad; bad &= bad - 1) sum += wgrad_terms(x, b0 + __builtin_ctz(bad), ch, tap, c, row);
         }
-        (is_db ? db : dw)[i] = t;
+        t = (float)(sum + __shfl_xor(sum, 32));
     }
+    if (row == 0 && i < n) (is_db ? db : dw)[i] = t;
 }
 
 // wt[ci][tap][co] = w[co][tap][ci] (bf16), the weights of the input-gradient convolution.
@@ -1382,11 +1416,13 @@ learn::WgradShape wgrad_shape(const learn::Vol& vol, int pairs, int nparts, doub
     return best;
 }
 
-int launch_wgrad(int nparts, hipStream_t s, const uint16_t* in, int in_stride, int in_coff, const uint16_t* dy,
-                 int dy_stride, int dy_coff, float* part, float* part_db, learn::Vol vol, int cin, int cout) {
+learn::WgradTensors launch_wgrad(int nparts, hipStream_t s, const uint16_t* in, int in_stride, int in_coff, const uint16_t* dy,
+                                 int dy_stride, int dy_coff, float* part, float* part_db, learn::Vol vol, int cin, int cout) {
     const int pairs = cout / 16 * ((cin + 15) / 16);
     double cost = 0.0;
     learn::WgradShape sh = wgrad_shape(vol, pairs, nparts, cost);
+    sh.slice = (int64_t)vol.H * vol.W, sh.row = vol.W, sh.col = 1;
+    sh.tap_slice = 9, sh.tap_row = 3, sh.tap_col = 1;
     // A volume of few short rows in few parts is a chain of short steps, or of padding; with its axes in another order it may
     // be few long ones (16 -> 16 channels in one part: 64 x 3 x 3 52 and 12, 31 x 48 x 1 38 and 17 us).  Voxels then come
     // one by one from afar, so the other order has to promise a third less (and is not looked for where no order can).
@@ -1416,7 +1452,7 @@ int launch_wgrad(int nparts, hipStream_t s, const uint16_t* in, int in_stride, i
     allow_lds((const void*)kernel, g_wgrad_devices[2 * big + perm]);
     hipLaunchKernelGGL(kernel, dim3((sh.parts * pairs + 7) / 8 * 8), dim3(learn::kWgThreads), sh.lds, s, in, in_stride,
                        in_coff, dy, dy_stride, dy_coff, part, part_db, vol, cin, cout, sh);
-    return sh.parts;
+    return {in + in_coff, dy + dy_coff, in_stride, dy_stride, cin, vol, sh};
 }
 constexpr int kBrickD = 4;
 struct ConvArgs {
@@ -1547,13 +1583,11 @@ int das_conv3d_wgrad(const void* in, int in_stride, int in_coff, const void* dy,
     hipStream_t s = reinterpret_cast<hipStream_t>(stream);
     float* part = work;
     float* part_db = work + (int64_t)nparts * nw;
-    const int parts = launch_wgrad(nparts, s, reinterpret_cast<const uint16_t*>(in), in_stride, in_coff,
-                                   reinterpret_cast<const uint16_t*>(dy), dy_stride, dy_coff, part, part_db,
-                                   learn::Vol{D, H, W}, cin, cout);
-    const learn::WgradTensors tensors{reinterpret_cast<const uint16_t*>(in) + in_coff, reinterpret_cast<const uint16_t*>(dy) + dy_coff,
-                                      in_stride, dy_stride, learn::Vol{D, H, W}, cin};
+    const learn::WgradTensors tensors = launch_wgrad(nparts, s, reinterpret_cast<const uint16_t*>(in), in_stride, in_coff,
+                                                     reinterpret_cast<const uint16_t*>(dy), dy_stride, dy_coff, part, part_db,
+                                                     learn::Vol{D, H, W}, cin, cout);
     hipLaunchKernelGGL(learn::reduce_parts_kernel, dim3(blocks_for(nw, 32) + blocks_for(cout, 32)), dim3(256), 0, s, part,
-                       part_db, parts, nw, (int)blocks_for(nw, 32), cout, dw, db, tensors);
+                       part_db, tensors.sh.parts, nw, (int)blocks_for(nw, 32), cout, dw, db, tensors);
     return launch_status("wgrad launch failed");
 }
 
